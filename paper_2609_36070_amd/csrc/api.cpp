@@ -24,7 +24,7 @@ struct Layout {
     size_t err, blockcounts, blockbase, blockflags, wrt, rpart, rowidx, wperm, zeros, fused;
     size_t prefix_total;
     size_t acc, coff;          // ring only: fp32 per-token accumulator, window regions
-    size_t A, B, H, Yexp, As, Bs, Hs, Ysh;
+    size_t A, B, H, Yexp, As, Bs, Hs, Ysh, part, part_s;
     size_t fwd_total;
     size_t dA, dB, Hw, dgpart, dg, dZ, dXperm, dAs, dBs, dXsh, dwr_part, dzs, wrs, xtt;
     size_t dytt;
@@ -80,6 +80,10 @@ Layout make_layout(const moe_shape &s, long ring_rows = -1) {
     L.Bs = take(T * fs * 2);
     L.Hs = take(T * fs * 2);
     L.Ysh = take(T * d * 2);
+    // small batches with dense routing: the down products before their sum, fp32
+    const bool part = ring_rows < 0 && s.k == s.E && skinny_tiles((long)T, (long)R, (int)E) > 0;
+    L.part = take(part ? R * d * 4 : 0);
+    L.part_s = take(part && fs > 0 ? T * d * 4 : 0);
     L.fwd_total = o;
     L.dg_parts = (int)(f / (size_t)gemm_tile_n());
     L.dA = take(Ra * f * 2);
@@ -337,6 +341,61 @@ hipError_t shared_down(const moe_shape &sh, const Layout &L, void *ws, const moe
 // any window that starts at position 0 (its regions start where the plan's
 // do) a gathered row is the position minus the region's start.
 bool dense_routing(const moe_shape &sh) { return sh.k == sh.E; }
+
+// Inference on a small batch takes the streaming kernels of skinny.hip.  A
+// forward that keeps its activations does not: the bounded-memory windows,
+// which must reproduce them bitwise, run the tile GEMMs.
+int small_tiles(const moe_shape &sh, int save) {
+    const int64_t R = sh.T * sh.k, lim = int64_t(1) << 32;   // 32-bit row offsets
+    if (save || sh.T * sh.d >= lim || R * sh.f >= lim || sh.T * sh.f_shared >= lim) return 0;
+    return skinny_tiles((long)sh.T, (long)R, (int)sh.E);
+}
+
+// The forward of a small batch: up/gate and down of every routed expert and
+// the shared one in a launch each, then the sum over each token's experts.
+hipError_t small_forward(const moe_shape &sh, const Layout &L, void *ws, const moe_bf16 *X,
+                         const moe_weights *w, const float *topk_w, const moe_plan_bufs *plan,
+                         moe_bf16 *Y, int tt, const StageMarks &mk, hipStream_t s) {
+    const int T = (int)sh.T, d = (int)sh.d, E = (int)sh.E, k = (int)sh.k, f = (int)sh.f;
+    const int fs = (int)sh.f_shared, R = T * k;
+    const bool dense = dense_routing(sh);
+    SkinnyArgs g;
+    g.offsets = plan->offsets; g.perm = plan->perm;
+    g.E = E; g.T = T; g.k = k; g.R = R;
+    SkinnyArgs u = g;
+    u.A = X; u.lda = d; u.a_nrows = T; u.K = d; u.N = f;
+    u.B = w->W_gate; u.B2 = w->W_up; u.ldb = f; u.b_estride = (long)d * f;
+    u.C = at<uint16_t>(ws, L.H); u.ldc = f;
+    u.row_w = dense ? topk_w : nullptr;
+    if (fs > 0) {
+        u.As = X; u.lda_s = d; u.Ks = d; u.Ns = fs;
+        u.Bs = w->Wg_s; u.Bs2 = w->Wu_s; u.ldb_s = fs;
+        u.Cs = at<uint16_t>(ws, L.Hs); u.ldc_s = fs;
+    }
+    hipError_t e = launch_skinny_up(u, tt, s);
+    if (e != hipSuccess) return e;
+    if ((e = mk.mark(2)) != hipSuccess || (e = mk.mark(3)) != hipSuccess) return e;
+    SkinnyArgs n = g;
+    n.A = at<uint16_t>(ws, L.H); n.lda = f; n.a_nrows = R; n.K = f; n.N = d;
+    n.B = w->W_down; n.ldb = d; n.b_estride = (long)f * d;
+    n.ldc = d;
+    if (dense) n.Cf = at<float>(ws, L.part);
+    else n.C = at<uint16_t>(ws, L.Yexp);
+    if (fs > 0) {
+        n.As = at<uint16_t>(ws, L.Hs); n.lda_s = fs; n.Ks = fs; n.Ns = d;
+        n.Bs = w->Wd_s; n.ldb_s = d; n.ldc_s = d;
+        if (dense) n.Cfs = at<float>(ws, L.part_s);
+        else n.Cs = at<uint16_t>(ws, L.Ysh);
+    }
+    if ((e = launch_skinny_down(n, tt, s)) != hipSuccess) return e;
+    if ((e = mk.mark(4)) != hipSuccess || (e = mk.mark(5)) != hipSuccess) return e;
+    if (dense)
+        e = launch_dense_sum(n.Cf, n.Cfs, plan->offsets, E, T, R, d, Y, s);
+    else
+        e = launch_combine(n.C, n.Cs, topk_w, plan->route_pos, T, d, k, Y, s);
+    if (e != hipSuccess) return e;
+    return mk.mark(6);
+}
 
 // Positions [w0, w1) of the routed buffer, with the expert regions clipped
 // to it.  Per-route activation rows live at row p - w0 of their region, so
@@ -825,6 +884,11 @@ moe_status moe_forward(const moe_shape *shape, const moe_bf16 *X, const moe_weig
     const StageMarks mk{events, s};
 
     MOE_TRY(mk.mark(0));
+    if (const int tt = small_tiles(*shape, save_for_backward)) {
+        MOE_TRY(mk.mark(1));
+        MOE_TRY(small_forward(*shape, L, ws, X, weights, topk_w, plan, Y, tt, mk, s));
+        return MOE_OK;
+    }
     MOE_TRY(launch_prep(plan->perm, plan->offsets, E, topk_w, k, T, at<int>(ws, L.rowidx),
                         at<float>(ws, L.wperm), at<uint16_t>(ws, L.zeros), s));
     MOE_TRY(mk.mark(1));
@@ -874,6 +938,11 @@ moe_status moe_forward_fused(const moe_shape *shape, const moe_bf16 *X, const mo
     const long R = (long)T * k;
     const Window all{plan->offsets, 0, (int)R};
     const bool save = save_for_backward != 0;
+    // a small batch has nothing to overlap: moe_forward's launches
+    if (const int tt = small_tiles(*shape, save_for_backward)) {
+        MOE_TRY(small_forward(*shape, L, ws, X, weights, topk_w, plan, Y, tt, StageMarks{nullptr, s}, s));
+        return MOE_OK;
+    }
 
     MOE_TRY(launch_prep(plan->perm, plan->offsets, E, topk_w, k, T, at<int>(ws, L.rowidx),
                         at<float>(ws, L.wperm), at<uint16_t>(ws, L.zeros), s));
@@ -990,6 +1059,11 @@ moe_status moe_forward_ring(const moe_shape *shape, const moe_bf16 *X, const moe
     const int nwin = ring_windows(*shape, ring_rows);
     int *coff = at<int>(ws, L.coff);
 
+    const int tt = nwin == 1 && !dense_routing(*shape) ? small_tiles(*shape, save_for_backward) : 0;
+    if (tt) {   // one window holds every route: the one-pass forward
+        MOE_TRY(small_forward(*shape, L, ws, X, weights, topk_w, plan, Y, tt, StageMarks{nullptr, s}, s));
+        return MOE_OK;
+    }
     MOE_TRY(launch_prep(plan->perm, plan->offsets, E, topk_w, k, T, at<int>(ws, L.rowidx),
                         at<float>(ws, L.wperm), at<uint16_t>(ws, L.zeros), s));
     if (ring_folds(*shape, ring_rows)) {

@@ -131,6 +131,38 @@ hipError_t launch_fused_forward(const GemmArgs &up_s, const GemmArgs &up_r, cons
 hipError_t launch_gemm_wgrad_batch(const GemmArgs *wg, int nw, int groups, const GemmArgs *up,
                                    long up_rows, hipStream_t st, const int *modes = nullptr);
 
+// Expert FFN products of small batches (skinny.hip): the routed experts' rows
+// of the plan and, when Ns > 0, the shared expert's T rows in one launch.
+enum SkinnyMode { SK_UP = 0, SK_DOWN = 1, SK_DOWN_PART = 2 };
+struct SkinnyArgs {
+    const uint16_t *A = nullptr;       // up: X by token; down: H by plan row
+    long lda = 0;
+    int a_nrows = 1;
+    const int *perm = nullptr;         // up: route of each plan row (token = route / k)
+    const float *row_w = nullptr;      // up with dense routing: gate weight per route, scales H
+    const uint16_t *B = nullptr;       // [E][K][N] weights (gate), B2: up
+    const uint16_t *B2 = nullptr;
+    long ldb = 0, b_estride = 0;
+    const int *offsets = nullptr;
+    int E = 0, T = 0, k = 1, R = 0, K = 0, N = 0;
+    uint16_t *C = nullptr;             // up: H; down: Yexp
+    float *Cf = nullptr;               // down with dense routing: fp32 products instead
+    long ldc = 0;
+    const uint16_t *As = nullptr, *Bs = nullptr, *Bs2 = nullptr;
+    long lda_s = 0, ldb_s = 0, ldc_s = 0;
+    int Ks = 0, Ns = 0;
+    uint16_t *Cs = nullptr;
+    float *Cfs = nullptr;
+    int nshared = 0;                   // set by the launcher: workgroups of the shared expert
+};
+// 16-row tiles per workgroup for T tokens and R routes, 0: not a small batch.
+int skinny_tiles(long T, long R, int E);
+hipError_t launch_skinny_up(const SkinnyArgs &g, int tt, hipStream_t st);
+hipError_t launch_skinny_down(const SkinnyArgs &g, int tt, hipStream_t st);
+// Dense routing: Y from the fp32 down products (part [R][d] by plan row, part_s [T][d] or null).
+hipError_t launch_dense_sum(const float *part, const float *part_s, const int *offsets, int E, int T,
+                            int R, int d, uint16_t *Y, hipStream_t st);
+
 int route_epad(int E);
 // Scratch of the split router (many experts): fp32 partial logits of its d
 // slices; 0 for shapes on the one-pass router.

@@ -1,0 +1,57 @@
+"""GPU parity of inference on small batches (the streaming expert kernels):
+every output element against the oracle at the edges of their tiles.
+
+The rule is: not kept for a backward, and T <= 16 (16-row tiles) or at most 64
+routes per expert on average (64-row tiles).  Shapes lie on both sides of each
+bound, with empty experts, experts of one row, of a whole tile and one row more.
+"""
+import pytest
+import torch
+
+from paper_2609_36070_amd.layer import DeviceLayer
+from paper_2609_36070_amd.workloads import Workload, make_inputs
+from tests.parity import assert_close, to_np
+from tests.test_gpu_small import forward_parity
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("w", [
+    # 16-row tiles, one token; dense routing with a shared expert of another width
+    Workload("one_dense", T=1, d=256, E=4, k=4, f=256, f_s=512, bias_std=0.5),
+    Workload("sixteen", T=16, d=768, E=8, k=3, f=256),                # a whole 16-row tile at most
+    Workload("seventeen", T=17, d=512, E=6, k=5, f=768, f_s=256, bias_std=1.0),   # first 64-row tiles
+    Workload("one_per_expert", T=40, d=256, E=200, k=1, f=512),       # single rows, empty experts
+    Workload("k16", T=50, d=1280, E=128, k=16, f=256, bias_std=0.5),
+    Workload("dense_64", T=64, d=512, E=5, k=5, f=512, f_s=256),      # a whole 64-row tile per expert
+    Workload("dense_65", T=65, d=512, E=5, k=5, f=512, f_s=256),      # past the bound: tile GEMMs
+    Workload("dense_9", T=33, d=256, E=9, k=9, f=256),                # the sum over more than 8 experts
+    Workload("skewed", T=250, d=256, E=16, k=4, f=256, bias_std=2.0),   # several 64-row tiles and empties
+    Workload("mean_64", T=128, d=256, E=4, k=2, f=512, f_s=512),      # R = 64 E exactly
+], ids=lambda w: w.name)
+def test_small_batch_parity(w):
+    forward_parity(w, seed=31)
+
+
+@pytest.mark.parametrize("w", [
+    Workload("sparse", T=48, d=512, E=16, k=4, f=256, f_s=256, bias_std=1.0),
+    Workload("dense", T=48, d=512, E=4, k=4, f=256, f_s=256),
+], ids=lambda w: w.name)
+def test_small_batch_against_tile_gemms(w):
+    """The same layer keeping its activations runs the tile GEMMs: Y differs by
+    summation order and the roundings it moves (one bf16 step of the largest
+    value, 2^-8 relative, at H and at Y each)."""
+    inp = make_inputs(w, 33)
+    L = DeviceLayer(w, inp)
+    L.step()
+    y = L.Y.clone()
+    inp["dY"] = inp["X"]
+    K = DeviceLayer(w, inp, with_backward=True)
+    K.route(); K.plan(); K.forward()
+    torch.cuda.synchronize()
+    assert_close("Y (small batch vs tiles)", to_np(y), to_np(K.Y), rel=2 ** -7)
+    for _ in range(2):       # repeats bitwise, with the workspace overwritten between
+        L.ws.fill_(255)
+        L.step()
+        torch.cuda.synchronize()
+        assert torch.equal(L.Y, y)
