@@ -10,7 +10,8 @@
 // order, so the result is deterministic.  128 or more experts
 // (route_split_kernel, route_reduce_kernel): 128-token tiles over slices of
 // the d axis staged through LDS, partial tiles added in slice order by a
-// second kernel.  The selection runs on groups of lanes per token.
+// second kernel.  Up to 2048 tokens one launch on W_r as it lies
+// (route_direct_kernel).  The selection runs on groups of lanes per token.
 #include "common.h"
 #include "kernels.h"
 
@@ -506,6 +507,111 @@ __global__ __launch_bounds__(256) void route_reduce_kernel(const float *__restri
     select_block<EPAD>(&zs[0][0], EPAD + 1, RR_BT, 4, t0, T, E, k, topk_idx, topk_w);
 }
 
+
+// ---------------------------------------------------------------------------
+// Router of small batches: one launch, no transposed copy of W_r.  A call of
+// a few tokens is a chain of latencies (the transpose's launch and round trip,
+// then the loads of a block, then the selection), so the block reads W_r as it
+// lies, [d][E], and holds enough loads to cover its share of d in one or two
+// round trips.  16 tokens per block; the d axis goes to the waves in steps of
+// 32, dealt round-robin.  In a step, lane (g, r) loads its CPL = E_pad / 16
+// consecutive expert columns CPL r .. of the 8 rows 8 g + j and transposes
+// them in registers (v_perm_b32) into the row operands of CPL
+// v_mfma_f32_16x16x32_bf16: product i holds expert CPL r + i in row r.  The
+// tokens are the column operand.  The wave partials are added in wave order.
+template <int N> struct RdVec;
+template <> struct RdVec<1> { typedef uint16_t T; };
+template <> struct RdVec<2> { typedef uint32_t T; };
+template <> struct RdVec<4> { typedef u32x2_t T; };
+template <> struct RdVec<8> { typedef u32x4_t T; };
+DEV uint32_t rd_word(uint16_t v, int) { return v; }
+DEV uint32_t rd_word(uint32_t v, int) { return v; }
+DEV uint32_t rd_word(const u32x2_t &v, int i) { return v[i]; }
+DEV uint32_t rd_word(const u32x4_t &v, int i) { return v[i]; }
+
+constexpr int rd_waves(int EPAD) { return EPAD <= 64 ? 16 : 8; }
+
+template <int EPAD>
+__global__ __launch_bounds__(64 * rd_waves(EPAD)) void route_direct_kernel(
+        const uint16_t *__restrict__ X, const uint16_t *__restrict__ Wr, const float *__restrict__ bias,
+        float *__restrict__ logits, int *__restrict__ topk_idx, float *__restrict__ topk_w, int T, int d,
+        int E, int k) {
+    constexpr int NW = rd_waves(EPAD), BT = 16;
+    constexpr int CPL = EPAD / 16, VW = CPL < 8 ? CPL : 8, NV = CPL / VW;
+    constexpr int U = EPAD <= 32 ? 8 : EPAD <= 128 ? 4 : 2;   // steps in flight per wave
+    typedef typename RdVec<VW>::T wvec;
+    __shared__ float red[NW][BT][EPAD + 1];
+    __shared__ float zs[BT][EPAD + 1];
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    const int g = l >> 4, r = l & 15;
+    const int t0 = blockIdx.x * BT;
+    const int nsteps = d / 32;
+
+    // columns past the experts re-read the last ones; their logits are not used
+    int col[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) col[v] = min(CPL * r + VW * v, E - VW);
+    const uint16_t *xrow = X + (long)min(t0 + r, T - 1) * d;
+
+    f32x4_t acc[CPL];
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int s0 = w; s0 < nsteps; s0 += NW * U) {
+        wvec wv[U][8][NV];
+        u32x4_t xv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int kk = 32 * min(s0 + NW * u, nsteps - 1) + 8 * g;
+            xv[u] = ld_u32x4(xrow + kk);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+#pragma unroll
+                for (int v = 0; v < NV; ++v)
+                    wv[u][j][v] = *reinterpret_cast<const wvec *>(Wr + (long)(kk + j) * E + col[v]);
+        }
+        __builtin_amdgcn_sched_barrier(0);   // every load before the first use
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (s0 + NW * u >= nsteps) break;
+#pragma unroll
+            for (int i = 0; i < CPL; ++i) {
+                const int v = i / VW, c = i % VW;
+                u32x4_t a;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    a[q] = __builtin_amdgcn_perm(rd_word(wv[u][2 * q + 1][v], c >> 1),
+                                                 rd_word(wv[u][2 * q][v], c >> 1),
+                                                 (c & 1) ? 0x07060302u : 0x05040100u);
+                acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
+                                                                 __builtin_bit_cast(bf16x8_t, xv[u]),
+                                                                 acc[i], 0, 0, 0);
+            }
+        }
+    }
+    // lane (g, r) register q of product i: expert CPL (4 g + q) + i of token r
+#pragma unroll
+    for (int i = 0; i < CPL; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) red[w][r][CPL * (4 * g + q) + i] = acc[i][q];
+    __syncthreads();
+    static_assert((64 * NW) % EPAD == 0, "one expert column per thread");
+    const int ecol = threadIdx.x % EPAD;
+    const float bz = (bias && ecol < E) ? bias[ecol] : 0.f;
+    for (int i = threadIdx.x; i < BT * EPAD; i += 64 * NW) {
+        const int tt = i / EPAD;
+        float z = red[0][tt][ecol] + red[1][tt][ecol];
+#pragma unroll
+        for (int v = 2; v < NW; ++v) z = z + red[v][tt][ecol];
+        if (ecol < E) {
+            if (bias) z = z + bz;
+            if (t0 + tt < T) logits[(long)(t0 + tt) * E + ecol] = z;
+            zs[tt][ecol] = z;
+        }
+    }
+    __syncthreads();
+    select_block<EPAD>(&zs[0][0], EPAD + 1, BT, NW, t0, T, E, k, topk_idx, topk_w);
+}
+
 }  // namespace
 
 int route_epad(int E) {
@@ -513,6 +619,13 @@ int route_epad(int E) {
     while (p < E) p *= 2;
     return p;
 }
+
+// Tokens up to which the one-launch router serves: it re-reads W_r per 16
+// tokens, and larger batches keep their logits' summation order.  us against
+// the other routers: 32 experts, d 4096: 1 token 8.7 / 16.2, 1000 11.7 / 19.3,
+// 2000 12.0 / 19.4; 128 experts, d 2048: 1 token 10.9 / 16.4, 1000 14.0 / 21.1;
+// 200 experts: 1000 tokens 23.5 / 33.4.
+constexpr int ROUTE_DIRECT_MAX = 2048;
 
 // Padded expert counts from which the split router runs.
 constexpr int ROUTE_SPLIT_MIN = 128;
@@ -536,6 +649,22 @@ hipError_t launch_route(const uint16_t *X, const uint16_t *W_r, const float *bia
                         int *topk_idx, float *topk_w, uint16_t *WrT, float *part, int T,
                         int d, int E, int k, hipStream_t st) {
     const int EPAD = route_epad(E);
+    // (its loads of several expert columns need them aligned in every row)
+    if (T > 0 && T <= ROUTE_DIRECT_MAX && E % (EPAD / 16 < 8 ? EPAD / 16 : 8) == 0) {
+        const dim3 grid((unsigned)((T + 15) / 16)), block(64 * rd_waves(EPAD));
+#define ROUTE_DIRECT(EP) \
+    route_direct_kernel<EP><<<grid, block, 0, st>>>(X, W_r, bias, logits, topk_idx, topk_w, T, d, E, k)
+        switch (EPAD) {
+            case 16: ROUTE_DIRECT(16); break;
+            case 32: ROUTE_DIRECT(32); break;
+            case 64: ROUTE_DIRECT(64); break;
+            case 128: ROUTE_DIRECT(128); break;
+            case 256: ROUTE_DIRECT(256); break;
+            default: return hipErrorInvalidValue;
+        }
+#undef ROUTE_DIRECT
+        return hipGetLastError();
+    }
     const int S = route_split_slices(T, d, E);
     wr_transpose_kernel<<<dim3((unsigned)((d + 31) / 32), (unsigned)((EPAD + 63) / 64)), dim3(256), 0,
                           st>>>(W_r, WrT, d, E, EPAD);
