@@ -121,6 +121,11 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint16_t *__restrict
 // dg[p] = sum over n-tiles of the partial <dh', h> (fixed order), then the
 // restricted-softmax backward per token:
 //   dZ[t,e_s] = w_s (dg_s - sum_s' w_s' dg_s'),  zero for unselected experts.
+// 16 lanes per token: lane s sums the partials of slot s, so a token's chains
+// of loads (position, then partials) run side by side; the sum over the slots
+// is taken in slot order; then the lanes write the dZ row 16 experts at a
+// time, coalesced.  One thread per token took 22 us at 4001 tokens to 32
+// experts (16 blocks of serial chains).
 __global__ __launch_bounds__(256) void softmax_bwd_kernel(const float *__restrict__ dgpart,
                                                           int nparts,
                                                           const int *__restrict__ route_pos,
@@ -129,37 +134,59 @@ __global__ __launch_bounds__(256) void softmax_bwd_kernel(const float *__restric
                                                           int k, int E, int R,
                                                           float *__restrict__ dg_out,
                                                           float *__restrict__ dZ) {
-    const int t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= T) return;
-    float dg[16], wt[16];
-    float swdg = 0.f;
+    const int t = blockIdx.x * 16 + (threadIdx.x >> 4), s = threadIdx.x & 15;
+    const bool live = t < T && s < k;
+    float dg = 0.f, wt = 0.f;
+    int e = -1;
+    if (live) {
+        const long j = (long)t * k + s;
+        const int p = route_pos[j];
+        wt = topk_w[j];
+        e = topk_idx[j];
+        if (p >= 0 && p < R) {
+            for (int q0 = 0; q0 < nparts; q0 += 8) {
+                float v[8];
 #pragma unroll
-    for (int s = 0; s < 16; ++s) {
-        dg[s] = 0.f;
-        wt[s] = 0.f;
-        if (s < k) {
-            const int p = route_pos[(long)t * k + s];
-            wt[s] = topk_w[(long)t * k + s];
-            if (p >= 0 && p < R) {
-                float acc = 0.f;
-                for (int q = 0; q < nparts; ++q) acc = acc + dgpart[(long)p * nparts + q];
-                dg[s] = acc;
-                dg_out[p] = acc;
+                for (int q = 0; q < 8; ++q)
+                    v[q] = q0 + q < nparts ? dgpart[(long)p * nparts + q0 + q] : 0.f;
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    if (q0 + q < nparts) dg = dg + v[q];
             }
-            swdg = swdg + wt[s] * dg[s];
+            dg_out[p] = dg;
         }
     }
-    for (int e = 0; e < E; ++e) dZ[(long)t * E + e] = 0.f;
-#pragma unroll
-    for (int s = 0; s < 16; ++s) {
-        if (s < k) {
-            const int e = topk_idx[(long)t * k + s];
-            if (e >= 0 && e < E) dZ[(long)t * E + e] = wt[s] * (dg[s] - swdg);
+    float swdg = 0.f;
+    for (int i = 0; i < k; ++i) {
+        const float wi = __shfl(wt, i, 16), di = __shfl(dg, i, 16);
+        swdg = swdg + wi * di;
+    }
+    const float z = wt * (dg - swdg);
+    for (int e0 = 0; e0 < E; e0 += 16) {
+        float v = 0.f;
+        for (int i = 0; i < k; ++i) {
+            const int ei = __shfl(e, i, 16);
+            const float zi = __shfl(z, i, 16);
+            if (ei == e0 + s) v = zi;
         }
+        if (t < T && e0 + s < E) dZ[(long)t * E + e0 + s] = v;
     }
 }
 
 // dX[t] = dXsh[t] + sum_slot dXperm[route_pos[t*k+slot]] + sum_e dZ[t,e] W_r[:,e]
+// (dXacc: the shared-expert and routed terms already summed per token).
+//
+// The router term is a product of depth E whose W_r, read per token, is
+// larger than the k rows the token gathers (32 experts, d 4096: 256 KB from L2
+// against 64 KB; 258 us at 4001 tokens).  So a block takes 16 tokens and RC_COLS
+// columns and runs it on v_mfma_f32_16x16x32_bf16: dZ is split into three bf16
+// parts whose sum is the fp32 value (8 + 8 + 8 significant bits), each product
+// with a bf16 weight is exact in fp32, and the accumulation is fp32.  W_r rows
+// [d][E] are contiguous along the contraction, so they are the column operand
+// as they lie.  The term crosses to the gathering threads (8 columns of one
+// token each) through LDS.
+constexpr int RC_COLS = 512;
+
 __global__ __launch_bounds__(256) void reverse_combine_kernel(const uint16_t *__restrict__ dXperm,
                                                               const uint16_t *__restrict__ dXsh,
                                                               const float *__restrict__ dZ,
@@ -168,185 +195,114 @@ __global__ __launch_bounds__(256) void reverse_combine_kernel(const uint16_t *__
                                                               int T, int d, int k, int E, int R,
                                                               const float *__restrict__ dXacc,
                                                               uint16_t *__restrict__ dX) {
-    __shared__ float dz[256];
-    const int nc = d / 8;
-    for (int t = blockIdx.x; t < T; t += gridDim.x) {
-        __syncthreads();
-        for (int e = threadIdx.x; e < E; e += 256) dz[e] = dZ[(long)t * E + e];
-        __syncthreads();
-        int pos[16];
-#pragma unroll
-        for (int s = 0; s < 16; ++s) {
-            pos[s] = -1;
-            if (s < k) {
-                const int p = route_pos[(long)t * k + s];
-                pos[s] = (p >= 0 && p < R) ? p : -1;
-            }
-        }
-        for (int c = threadIdx.x; c < nc; c += 256) {
-            float acc[8];
-            if (dXacc) {
-                // shared-expert and routed terms already summed per token
-                // (bounded-memory backward)
-                const f32x4_t lo = *reinterpret_cast<const f32x4_t *>(dXacc + (long)t * d + 8 * c);
-                const f32x4_t hi = *reinterpret_cast<const f32x4_t *>(dXacc + (long)t * d + 8 * c + 4);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    acc[q] = lo[q];
-                    acc[4 + q] = hi[q];
-                }
-            } else if (dXsh) {
-                const u32x4_t v = ld_u32x4(dXsh + (long)t * d + 8 * c);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    acc[2 * q] = bf_lo(v[q]);
-                    acc[2 * q + 1] = bf_hi(v[q]);
-                }
-            } else {
-#pragma unroll
-                for (int q = 0; q < 8; ++q) acc[q] = 0.f;
-            }
-            if (!dXacc) {
-                u32x4_t rows[16];   // all loads first, as in the combine
-#pragma unroll
-                for (int s = 0; s < 16; ++s)
-                    if (s < k) rows[s] = ld_u32x4(dXperm + (long)max(pos[s], 0) * d + 8 * c);
-#pragma unroll
-                for (int s = 0; s < 16; ++s) {
-                    if (s < k && pos[s] >= 0) {
-                        const u32x4_t v = rows[s];
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            acc[2 * q] = acc[2 * q] + bf_lo(v[q]);
-                            acc[2 * q + 1] = acc[2 * q + 1] + bf_hi(v[q]);
-                        }
-                    }
-                }
-            }
-            // router term: rows 8c..8c+7 of W_r, all experts
-            float racc[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) racc[q] = 0.f;
-            if ((E & 7) == 0) {
-                for (int e0 = 0; e0 < E; e0 += 8) {
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) {
-                        const u32x4_t wv = ld_u32x4(Wr + (long)(8 * c + q) * E + e0);
-#pragma unroll
-                        for (int h = 0; h < 4; ++h) {
-                            racc[q] = racc[q] + dz[e0 + 2 * h] * bf_lo(wv[h]);
-                            racc[q] = racc[q] + dz[e0 + 2 * h + 1] * bf_hi(wv[h]);
-                        }
-                    }
-                }
-            } else {
-                for (int e = 0; e < E; ++e) {
-#pragma unroll
-                    for (int q = 0; q < 8; ++q)
-                        racc[q] = racc[q] + dz[e] * bf2f(Wr[(long)(8 * c + q) * E + e]);
-                }
-            }
-            u32x4_t o;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                o[q] = pack_bf2(acc[2 * q] + racc[2 * q], acc[2 * q + 1] + racc[2 * q + 1]);
-            st_u32x4(dX + (long)t * d + 8 * c, o);
-        }
+    __shared__ __attribute__((aligned(16))) float rt[16][RC_COLS + 4];
+    __shared__ int spos[16 * 16];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int g = lane >> 4, r = lane & 15;
+    const int ncb = (d + RC_COLS - 1) / RC_COLS;
+    const int t0 = (int)(blockIdx.x / ncb) * 16, c0 = (int)(blockIdx.x % ncb) * RC_COLS;
+    const int ncols = min(RC_COLS, d - c0);      // a multiple of 256
+    if (tid < 16 * k) {
+        const int tt = tid / k;
+        const int p = t0 + tt < T ? route_pos[(long)t0 * k + tid] : -1;
+        spos[tid] = (p >= 0 && p < R) ? p : -1;
     }
-}
 
-// The same sum for a small expert count (E = 8 EG, EG <= 2): one thread owns
-// an 8-column chunk of dX for a group of tokens and keeps the 8 x E router
-// weights of its chunk in registers, so W_r is read once per group instead of
-// once per token; dZ rows are uniform loads.  The arithmetic and its order
-// are those of reverse_combine_kernel, so the results are identical.
-constexpr int RC_TG = 8;      // tokens per block
-constexpr int RC_BT = 128;    // threads per block, one column chunk each
-
-template <int EG>
-__global__ __launch_bounds__(RC_BT) void reverse_combine_small_e_kernel(
-        const uint16_t *__restrict__ dXperm, const uint16_t *__restrict__ dXsh,
-        const float *__restrict__ dZ, const uint16_t *__restrict__ Wr,
-        const int *__restrict__ route_pos, int T, int d, int k, int R,
-        const float *__restrict__ dXacc, uint16_t *__restrict__ dX) {
-    constexpr int E = 8 * EG;
-    const int nc = d / 8;
-    const int c = blockIdx.y * RC_BT + threadIdx.x;
-    if (c >= nc) return;   // nothing below synchronises the block
-    u32x4_t w[8][EG];
+    // router term: wave w takes ncols / 4 columns in tiles of 16
+    f32x4_t acc[RC_COLS / 64];
 #pragma unroll
-    for (int q = 0; q < 8; ++q)
+    for (int i = 0; i < RC_COLS / 64; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const int wc0 = c0 + w * (ncols / 4), ntile = ncols / 64;
+    const float *zrow = dZ + (long)min(t0 + r, T - 1) * E;
+    const bool vec = (E & 7) == 0;               // 16-byte W_r pieces
+    for (int e0 = 0; e0 < E; e0 += 32) {
+        const int eb = e0 + 8 * g;               // this lane's 8 experts
+        u32x4_t part[3];
+        {
+            float z[8];
 #pragma unroll
-        for (int g = 0; g < EG; ++g) w[q][g] = ld_u32x4(Wr + (long)(8 * c + q) * E + 8 * g);
-    const int t0 = blockIdx.x * RC_TG;
-    const int t1 = min(T, t0 + RC_TG);
-    for (int t = t0; t < t1; ++t) {
-        float dz[E];
+            for (int j = 0; j < 8; ++j) z[j] = eb + j < E ? zrow[eb + j] : 0.f;
 #pragma unroll
-        for (int e = 0; e < E; ++e) dz[e] = dZ[(long)t * E + e];
-        float acc[8];
-        if (dXacc) {
-            const f32x4_t lo = *reinterpret_cast<const f32x4_t *>(dXacc + (long)t * d + 8 * c);
-            const f32x4_t hi = *reinterpret_cast<const f32x4_t *>(dXacc + (long)t * d + 8 * c + 4);
+            for (int h = 0; h < 3; ++h)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                acc[q] = lo[q];
-                acc[4 + q] = hi[q];
-            }
-        } else {
-            int pos[16];
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t v = pack_bf2(z[2 * j], z[2 * j + 1]);
+                    part[h][j] = v;
+                    z[2 * j] -= bf_lo(v);
+                    z[2 * j + 1] -= bf_hi(v);
+                }
+        }
+        u32x4_t wv[RC_COLS / 64];
 #pragma unroll
-            for (int s2 = 0; s2 < 16; ++s2) {
-                pos[s2] = -1;
-                if (s2 < k) {
-                    const int p = route_pos[(long)t * k + s2];
-                    pos[s2] = (p >= 0 && p < R) ? p : -1;
+        for (int i = 0; i < RC_COLS / 64; ++i) {
+            wv[i] = u32x4_t{0, 0, 0, 0};
+            if (i < ntile && eb < E) {
+                const uint16_t *src = Wr + (long)(wc0 + 16 * i + r) * E + eb;
+                if (vec) {
+                    wv[i] = ld_u32x4(src);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        if (eb + j < E) wv[i][j >> 1] |= (uint32_t)src[j] << (16 * (j & 1));
                 }
             }
-            u32x4_t rows[16];
+        }
 #pragma unroll
-            for (int s2 = 0; s2 < 16; ++s2)
-                if (s2 < k) rows[s2] = ld_u32x4(dXperm + (long)max(pos[s2], 0) * d + 8 * c);
+        for (int i = 0; i < RC_COLS / 64; ++i)
+#pragma unroll
+            for (int h = 2; h >= 0; --h)         // the smallest part first
+                acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, part[h]),
+                                                                 __builtin_bit_cast(bf16x8_t, wv[i]),
+                                                                 acc[i], 0, 0, 0);
+    }
+    // lane (g, r) register q: token 4 g + q, column r of the tile
+#pragma unroll
+    for (int i = 0; i < RC_COLS / 64; ++i)
+        if (i < ntile)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) rt[4 * g + q][wc0 - c0 + 16 * i + r] = acc[i][q];
+    __syncthreads();
+
+    const int nc = ncols / 8;
+    for (int u = tid; u < 16 * nc; u += 256) {
+        const int tt = u / nc, t = t0 + tt, c = c0 + 8 * (u % nc);
+        if (t >= T) break;
+        float a[8];
+        if (dXacc) {
+            const f32x8 v = ld_f32x8(dXacc + (long)t * d + c);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) a[q] = v[q];
+        } else {
+            u32x4_t rows[16];   // all loads first, as in the combine
+#pragma unroll
+            for (int s = 0; s < 16; ++s)
+                if (s < k) rows[s] = ld_u32x4(dXperm + (long)max(spos[tt * k + s], 0) * d + c);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) a[q] = 0.f;
             if (dXsh) {
-                const u32x4_t v = ld_u32x4(dXsh + (long)t * d + 8 * c);
+                const u32x4_t v = ld_u32x4(dXsh + (long)t * d + c);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    acc[2 * q] = bf_lo(v[q]);
-                    acc[2 * q + 1] = bf_hi(v[q]);
+                    a[2 * q] = bf_lo(v[q]);
+                    a[2 * q + 1] = bf_hi(v[q]);
                 }
-            } else {
-#pragma unroll
-                for (int q = 0; q < 8; ++q) acc[q] = 0.f;
             }
 #pragma unroll
-            for (int s2 = 0; s2 < 16; ++s2) {
-                if (s2 < k && pos[s2] >= 0) {
-                    const u32x4_t v = rows[s2];
+            for (int s = 0; s < 16; ++s) {
+                if (s < k && spos[tt * k + s] >= 0) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        acc[2 * q] = acc[2 * q] + bf_lo(v[q]);
-                        acc[2 * q + 1] = acc[2 * q + 1] + bf_hi(v[q]);
+                        a[2 * q] = a[2 * q] + bf_lo(rows[s][q]);
+                        a[2 * q + 1] = a[2 * q + 1] + bf_hi(rows[s][q]);
                     }
                 }
             }
         }
-        float racc[8];
+        const f32x8 z = ld_f32x8(&rt[tt][c - c0]);
+        f32x8 o;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            racc[q] = 0.f;
-#pragma unroll
-            for (int g = 0; g < EG; ++g)
-#pragma unroll
-                for (int h = 0; h < 4; ++h) {
-                    racc[q] = racc[q] + dz[8 * g + 2 * h] * bf_lo(w[q][g][h]);
-                    racc[q] = racc[q] + dz[8 * g + 2 * h + 1] * bf_hi(w[q][g][h]);
-                }
-        }
-        u32x4_t o;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            o[q] = pack_bf2(acc[2 * q] + racc[2 * q], acc[2 * q + 1] + racc[2 * q + 1]);
-        st_u32x4(dX + (long)t * d + 8 * c, o);
+        for (int q = 0; q < 8; ++q) o[q] = a[q] + z[q];
+        st_u32x4(dX + (long)t * d + c, pack_bf8(o));
     }
 }
 
@@ -452,7 +408,10 @@ constexpr int DWR_TC = 256;             // tokens per chunk
 // DWR_TC tokens (4 steps of 64); each wave owns 64 columns (4 m-tiles).
 // X[64][256] tiles reach LDS by direct loads (global_load_lds_dwordx4, two
 // stages, the next step in flight while one is multiplied); the chunk's
-// split dZ is staged once per group of 8 experts.  X fragments come from the
+// split dZ is staged once.  A block multiplies each X fragment with G groups
+// of 8 experts, and grid z covers the experts past them, so X is read once
+// per 32 experts (it was once per 8, in turn: 30 us at 4001 tokens to 32
+// experts, 16 blocks' worth of columns).  X fragments come from the
 // transposing ds_read_b64_tr_b16, which hands each lane one column of a
 // 4 x 16 block.  X's LDS rows are 512 bytes with the 32-byte block index XOR
 // s(k) = (k & 3) | ((k >> 3) & 3) << 2, so the 16 rows one transposing read
@@ -482,12 +441,13 @@ DEV void dwm_wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
 
+template <int G>
 __global__ __launch_bounds__(256) void dwr_mfma_kernel(const uint16_t *__restrict__ X,
                                                        const float *__restrict__ dZ, int T, int d,
                                                        int E, float *__restrict__ part) {
     __shared__ __attribute__((aligned(16))) uint16_t xa[DWM_STEP * DWM_COLS];
     __shared__ __attribute__((aligned(16))) uint16_t xb[DWM_STEP * DWM_COLS];
-    __shared__ __attribute__((aligned(16))) uint16_t zsh[16 * DWM_ZLD];
+    __shared__ __attribute__((aligned(16))) uint16_t zsh[G * 16 * DWM_ZLD];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, r = lane & 15;
@@ -515,12 +475,15 @@ __global__ __launch_bounds__(256) void dwr_mfma_kernel(const uint16_t *__restric
                                              (DWM_LDS void *)(buf + (8 * wave + p) * 512), 16, 0, 0);
         }
     };
-    auto compute = [&](const uint16_t *buf, int st, f32x4_t (&acc)[4]) {
+    auto compute = [&](const uint16_t *buf, int st, f32x4_t (&acc)[G][4]) {
 #pragma unroll
         for (int ks = 0; ks < DWM_STEP / 32; ++ks) {
-            const bf16x8_t bz = __builtin_bit_cast(
-                bf16x8_t, *reinterpret_cast<const u32x4_t *>(
-                              &zsh[r * DWM_ZLD + DWM_STEP * st + 32 * ks + 8 * g]));
+            bf16x8_t bz[G];
+#pragma unroll
+            for (int gi = 0; gi < G; ++gi)
+                bz[gi] = __builtin_bit_cast(
+                    bf16x8_t, *reinterpret_cast<const u32x4_t *>(
+                                  &zsh[(16 * gi + r) * DWM_ZLD + DWM_STEP * st + 32 * ks + 8 * g]));
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt) {
                 const int cb = wave * 64 + 16 * mt;   // first column of the m-tile
@@ -533,63 +496,70 @@ __global__ __launch_bounds__(256) void dwr_mfma_kernel(const uint16_t *__restric
                 }
                 const bf16x8_t a = bf16x8_t{v[0][0], v[0][1], v[0][2], v[0][3],
                                             v[1][0], v[1][1], v[1][2], v[1][3]};
-                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bz, acc[mt], 0, 0, 0);
+#pragma unroll
+                for (int gi = 0; gi < G; ++gi)
+                    acc[gi][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bz[gi], acc[gi][mt], 0, 0, 0);
             }
         }
     };
 
-    for (int eg0 = 0; eg0 < E; eg0 += 8) {
-        // the chunk's dZ for experts eg0 .. eg0 + 7, split: rows 0-7 hi, 8-15 lo
-        {
-            // all 8 loads issued together (clamped in bounds), then masked
-            const int t = tc0 + tid;   // 256 threads = DWR_TC tokens
-            const float *zrow = dZ + (long)min(t, tc1 - 1) * E;
-            float v[8];
+    // this block's experts: 8 G from eg0
+    const int eg0 = 8 * G * blockIdx.z;
+    issue(xa, 0);
+    if (n > 1) issue(xb, 1);
+    // the chunk's dZ, split: rows 0-7 of a group hi, 8-15 lo
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = zrow[min(eg0 + e, E - 1)];
+    for (int gi = 0; gi < G; ++gi) {
+        // all 8 loads issued together (clamped in bounds), then masked
+        const int t = tc0 + tid;   // 256 threads = DWR_TC tokens
+        const float *zrow = dZ + (long)min(t, tc1 - 1) * E;
+        float v[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float z = (t < tc1 && eg0 + e < E) ? v[e] : 0.f;
-                const uint16_t hi = f2bf(z);
-                zsh[e * DWM_ZLD + tid] = hi;
-                zsh[(8 + e) * DWM_ZLD + tid] = f2bf(z - bf2f(hi));
-            }
+        for (int e = 0; e < 8; ++e) v[e] = zrow[min(eg0 + 8 * gi + e, E - 1)];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float z = (t < tc1 && eg0 + 8 * gi + e < E) ? v[e] : 0.f;
+            const uint16_t hi = f2bf(z);
+            zsh[(16 * gi + e) * DWM_ZLD + tid] = hi;
+            zsh[(16 * gi + 8 + e) * DWM_ZLD + tid] = f2bf(z - bf2f(hi));
         }
-        __syncthreads();
-        f32x4_t acc[4];
+    }
+    __syncthreads();   // also waits for the two steps in flight
+    f32x4_t acc[G][4];
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) acc[mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        issue(xa, 0);
-        if (n > 1) issue(xb, 1);
-        for (int st = 0; st < n; st += 2) {
-            // step st from xa: in flight are st and, if it exists, st + 1
-            if (st + 1 < n) dwm_wait_vmcnt<8>(); else dwm_wait_vmcnt<0>();
+    for (int gi = 0; gi < G; ++gi)
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) acc[gi][mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int st = 0; st < n; st += 2) {
+        // step st from xa: in flight are st and, if it exists, st + 1
+        if (st + 1 < n) dwm_wait_vmcnt<8>(); else dwm_wait_vmcnt<0>();
+        dwm_barrier();
+        compute(xa, st, acc);
+        dwm_barrier();
+        if (st + 2 < n) issue(xa, st + 2);
+        if (st + 1 < n) {
+            if (st + 2 < n) dwm_wait_vmcnt<8>(); else dwm_wait_vmcnt<0>();
             dwm_barrier();
-            compute(xa, st, acc);
+            compute(xb, st + 1, acc);
             dwm_barrier();
-            if (st + 2 < n) issue(xa, st + 2);
-            if (st + 1 < n) {
-                if (st + 2 < n) dwm_wait_vmcnt<8>(); else dwm_wait_vmcnt<0>();
-                dwm_barrier();
-                compute(xb, st + 1, acc);
-                dwm_barrier();
-                if (st + 3 < n) issue(xb, st + 3);
-            }
+            if (st + 3 < n) issue(xb, st + 3);
         }
-        // lane (g, r) holds columns 4g + q of each m-tile for n = r: hi for
-        // r < 8, lo for r >= 8; hi + lo, then the lane with r < 8 stores
+    }
+    // lane (g, r) holds columns 4g + q of each m-tile for n = r: hi for
+    // r < 8, lo for r >= 8; hi + lo, then the lane with r < 8 stores
+#pragma unroll
+    for (int gi = 0; gi < G; ++gi)
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const float lo = __shfl_xor(acc[mt][q], 8);
-                const int e = eg0 + r;
+                const float lo = __shfl_xor(acc[gi][mt][q], 8);
+                const int e = eg0 + 8 * gi + r;
                 if (r < 8 && e < E) {
                     const int i = i0 + wave * 64 + 16 * mt + 4 * g + q;
-                    part[((long)ch * d + i) * E + e] = acc[mt][q] + lo;
+                    part[((long)ch * d + i) * E + e] = acc[gi][mt][q] + lo;
                 }
             }
-    }
 }
 
 __global__ __launch_bounds__(256) void dwr_reduce_kernel(const float *__restrict__ part, int nch,
@@ -721,7 +691,7 @@ hipError_t launch_softmax_bwd(const float *dgpart, int nparts, const int *route_
                               const float *topk_w, const int *topk_idx, int T, int k, int E,
                               float *dg_out, float *dZ, hipStream_t st) {
     if (T == 0) return hipSuccess;
-    softmax_bwd_kernel<<<dim3((unsigned)((T + 255) / 256)), dim3(256), 0, st>>>(
+    softmax_bwd_kernel<<<dim3((unsigned)((T + 15) / 16)), dim3(256), 0, st>>>(
         dgpart, nparts, route_pos, topk_w, topk_idx, T, k, E, T * k, dg_out, dZ);
     return hipGetLastError();
 }
@@ -730,18 +700,9 @@ hipError_t launch_reverse_combine(const uint16_t *dXperm, const uint16_t *dXsh, 
                                   const uint16_t *W_r, const int *route_pos, int T, int d, int k,
                                   int E, const float *dXacc, uint16_t *dX, hipStream_t st) {
     if (T == 0) return hipSuccess;
-    if (E == 8 || E == 16) {
-        const dim3 grid((unsigned)((T + RC_TG - 1) / RC_TG), (unsigned)((d / 8 + RC_BT - 1) / RC_BT));
-        if (E == 8)
-            reverse_combine_small_e_kernel<1><<<grid, dim3(RC_BT), 0, st>>>(
-                dXperm, dXsh, dZ, W_r, route_pos, T, d, k, T * k, dXacc, dX);
-        else
-            reverse_combine_small_e_kernel<2><<<grid, dim3(RC_BT), 0, st>>>(
-                dXperm, dXsh, dZ, W_r, route_pos, T, d, k, T * k, dXacc, dX);
-        return hipGetLastError();
-    }
-    reverse_combine_kernel<<<dim3(rows_grid(T)), dim3(256), 0, st>>>(dXperm, dXsh, dZ, W_r, route_pos,
-                                                                      T, d, k, E, T * k, dXacc, dX);
+    const long grid = (long)((T + 15) / 16) * ((d + RC_COLS - 1) / RC_COLS);
+    reverse_combine_kernel<<<dim3((unsigned)grid), dim3(256), 0, st>>>(dXperm, dXsh, dZ, W_r, route_pos, T,
+                                                                       d, k, E, T * k, dXacc, dX);
     return hipGetLastError();
 }
 
@@ -765,8 +726,13 @@ hipError_t launch_dwr(const uint16_t *X, const float *dZ, int T, int d, int E, f
     const int nch = dwr_nchunks(T);
     const long n = (long)d * E;
     if (nch > 0) {
-        dim3 grid((unsigned)(d / DWM_COLS), (unsigned)nch);
-        dwr_mfma_kernel<<<grid, dim3(256), 0, st>>>(X, dZ, T, d, E, part);
+        // experts per pass over X: as many as the batch has, up to 32 (four
+        // accumulator groups; more would not fit beside the X stages)
+        const int G = E <= 8 ? 1 : E <= 16 ? 2 : 4;
+        dim3 grid((unsigned)(d / DWM_COLS), (unsigned)nch, (unsigned)((E + 8 * G - 1) / (8 * G)));
+        if (G == 1) dwr_mfma_kernel<1><<<grid, dim3(256), 0, st>>>(X, dZ, T, d, E, part);
+        else if (G == 2) dwr_mfma_kernel<2><<<grid, dim3(256), 0, st>>>(X, dZ, T, d, E, part);
+        else dwr_mfma_kernel<4><<<grid, dim3(256), 0, st>>>(X, dZ, T, d, E, part);
     }
     dwr_reduce_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st>>>(part, nch, n, dWr);
     return hipGetLastError();
