@@ -70,33 +70,55 @@ DEV u32x4_t pack_bf8(const f32x8 &v) {
 }
 
 // XCD-aware raster of the grouped GEMMs.  Workgroups are dealt to the 8 XCDs
-// round-robin (workgroup b runs on XCD b % 8).  The tiles are cut into groups
-// of RASTER_GM m-tiles x all n-tiles, walked m-tile fastest; group g goes to
-// XCD g % 8, and each XCD walks its groups in order.  The ~32 workgroups an
-// XCD runs at once then share RASTER_GM A panels and ~8 B panels in its L2,
-// and at any time the 8 XCDs work on 8 neighbouring groups, which read the
-// same expert's weights: those reads hit in the Infinity Cache instead of
-// each XCD streaming a different expert from HBM (3-7 % faster than giving
-// each XCD one contiguous run of groups).  Slots past the tiles return at once.
-constexpr int RASTER_GM = 4;
+// round-robin (workgroup b runs on XCD b % 8).  The tiles are ordered in
+// groups of RASTER_GM m-tiles x all n-tiles, walked m-tile fastest, and the
+// order is cut into chunks of RASTER_CHUNK = 32 tiles, about what an XCD runs
+// at once; chunk c goes to XCD c % 8.  A chunk shares RASTER_GM A panels and
+// ~8 B panels in its XCD's L2, and at any time the 8 XCDs work on 8
+// neighbouring chunks, which read the same expert's weights: those reads hit
+// in the Infinity Cache instead of each XCD streaming a different expert from
+// HBM (3-7 % faster than giving each XCD one contiguous run).  Dealing whole
+// groups instead left the XCDs uneven when there are few: 41 m-tiles x 12
+// n-tiles are 11 groups, so two XCDs ran three rounds while five ran one and
+// a half and the CUs were busy 58 % of the launch.  Whole forward, groups ->
+// chunks (us): 1000 tokens to 32 experts 580 -> 534; 4099 tokens to 8 experts
+// and a shared one 4027 -> 3062 (the shared and the folded down product are
+// 17 m-tiles: 5 groups on 8 XCDs); 16384 tokens unchanged.  Slots past the
+// tiles return at once.
+constexpr int RASTER_GM = 4, RASTER_CHUNK = 32;
 
-DEV bool map_tile(int b, int tiles_m, int ntn, int &mt, int &nt) {
-    constexpr int NX = 8, GM = RASTER_GM;
-    const int x = b % NX, j = b / NX;
-    const int tpg = GM * ntn;
-    const int group = (j / tpg) * NX + x;
-    const int within = j % tpg;
-    const int first = group * GM;
+// Place of tile number `group * RASTER_GM * ntn + within` of that order.
+DEV bool map_group_tile(int group, int within, int tiles_m, int ntn, int &mt, int &nt) {
+    const int first = group * RASTER_GM;
     if (first >= tiles_m) return false;
-    const int gm = min(GM, tiles_m - first);
+    const int gm = min(RASTER_GM, tiles_m - first);
     if (within >= gm * ntn) return false;
     mt = first + within % gm;
     nt = within / gm;
     return true;
 }
 
+DEV bool map_tile(int b, int tiles_m, int ntn, int &mt, int &nt) {
+    const int j = b / 8;
+    const int t = ((j / RASTER_CHUNK) * 8 + b % 8) * RASTER_CHUNK + j % RASTER_CHUNK;
+    const int tpg = RASTER_GM * ntn;
+    return map_group_tile(t / tpg, t % tpg, tiles_m, ntn, mt, nt);
+}
+
 // Workgroups of a launch whose tiles map_tile places.
 inline long raster_grid(long tiles_m, int ntn) {
+    const long tiles = (tiles_m + RASTER_GM - 1) / RASTER_GM * RASTER_GM * ntn;
+    return (tiles + 8 * RASTER_CHUNK - 1) / (8 * RASTER_CHUNK) * (8 * RASTER_CHUNK);
+}
+
+// The fused forward's raster: whole groups dealt to the XCDs, group g to XCD
+// g % 8, so that a tile and the tiles that wait for it can share an XCD.
+DEV bool map_tile_groups(int b, int tiles_m, int ntn, int &mt, int &nt) {
+    const int x = b % 8, j = b / 8;
+    const int tpg = RASTER_GM * ntn;
+    return map_group_tile((j / tpg) * 8 + x, j % tpg, tiles_m, ntn, mt, nt);
+}
+inline long raster_grid_groups(long tiles_m, int ntn) {
     const long groups = (tiles_m + RASTER_GM - 1) / RASTER_GM;
     return 8 * ((groups + 7) / 8) * RASTER_GM * ntn;
 }

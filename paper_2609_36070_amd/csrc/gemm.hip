@@ -233,7 +233,9 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
     if constexpr (Tr::GROUPED_ROWS) {
         const int ntn = (MODE == FWD_UP) ? g.N / (BN / 2) : g.N / BN;
         int mt = 0;
-        if (!map_tile(vb, g.tiles_m, ntn, mt, ntile)) return;
+        if (PERSISTENT ? !map_tile_groups(vb, g.tiles_m, ntn, mt, ntile)
+                       : !map_tile(vb, g.tiles_m, ntn, mt, ntile))
+            return;
         n0 = ntile * ((MODE == FWD_UP) ? BN / 2 : BN);
         if constexpr (GROUPED && PERSISTENT) {
             // the fused kernel keeps the grouped raster's prefix and the
@@ -1041,8 +1043,8 @@ hipError_t launch_gemm_wgrad_batch(const GemmArgs *wg, int nw, int groups, const
 // need nothing), the routed up/gate tiles, the shared down tiles, the
 // routed down tiles, and the combine of blocks of FUSED_TB tokens.  There is
 // one queue per XCD (workgroup index mod 8); queue x holds, for each GEMM,
-// exactly the tiles the XCD-aware raster gives XCD x in a launch of its own,
-// in the same order, so every tile keeps its L2 neighbours.  A down tile
+// every eighth group of the raster's tiles (map_tile_groups), so every tile
+// keeps its L2 neighbours.  A down tile
 // waits until all up/gate tiles of its m-tile slot have been published; a
 // combine block waits for the down tiles holding its tokens' routes.  Items
 // are taken in queue order and wait only on items earlier in some queue,
@@ -1301,7 +1303,7 @@ hipError_t launch_fused_forward(const GemmArgs &up_s, const GemmArgs &up_r, cons
     long at = 0;
     const int ntns[4] = {ntn_up_s, ntn_up_r, ntn_dn_s, ntn_dn_r};
     for (int i = 0; i < 4; ++i) {
-        fa.grid[i] = tiles[i] > 0 ? (int)raster_grid(fa.g[i].tiles_m, ntns[i]) : 0;
+        fa.grid[i] = tiles[i] > 0 ? (int)raster_grid_groups(fa.g[i].tiles_m, ntns[i]) : 0;
         fa.base[i] = (int)at;
         at += fa.grid[i] / 8;
     }

@@ -1,0 +1,57 @@
+"""The GEMM rasters place every tile exactly once (CPU: common.h's functions
+compiled for the host and walked over grids around their chunk and group sizes)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2609_36070_amd", "csrc")
+
+PROG = r"""
+#include <algorithm>
+#include <cstdio>
+#include <set>
+#include <utility>
+#define __host__
+#define __device__
+#define __forceinline__
+using std::min;
+#define DEV static inline
+%s
+template <class F> static int walk(F f, long grid, int tm, int ntn) {
+    std::set<std::pair<int, int>> seen;
+    for (long b = 0; b < grid; ++b) {
+        int mt = -1, nt = -1;
+        if (!f((int)b, tm, ntn, mt, nt)) continue;
+        if (mt < 0 || mt >= tm || nt < 0 || nt >= ntn || !seen.insert({mt, nt}).second) return 1;
+    }
+    return seen.size() == (size_t)tm * ntn ? 0 : 2;
+}
+int main() {
+    int bad = 0;
+    for (int tm : {1, 2, 3, 4, 5, 7, 8, 17, 31, 33, 41, 64, 130})
+        for (int ntn : {1, 2, 3, 5, 8, 12, 16, 28, 56}) {
+            if (walk(map_tile, raster_grid(tm, ntn), tm, ntn)) { std::printf("chunks %%d %%d\n", tm, ntn); ++bad; }
+            if (walk(map_tile_groups, raster_grid_groups(tm, ntn), tm, ntn)) { std::printf("groups %%d %%d\n", tm, ntn); ++bad; }
+            // chunks: no XCD holds more than one chunk above another
+            int n[8] = {0};
+            for (long b = 0; b < raster_grid(tm, ntn); ++b) {
+                int mt, nt;
+                n[b %% 8] += map_tile((int)b, tm, ntn, mt, nt);
+            }
+            if (*std::max_element(n, n + 8) - *std::min_element(n, n + 8) > RASTER_CHUNK) { std::printf("uneven %%d %%d\n", tm, ntn); ++bad; }
+        }
+    return bad;
+}
+"""
+
+
+@pytest.mark.skipif(not shutil.which("g++"), reason="needs a host compiler")
+def test_every_tile_placed_once(tmp_path):
+    src = open(os.path.join(CSRC, "common.h")).read()
+    part = src[src.index("constexpr int RASTER_GM"):src.index("// Weight-gradient raster.")]
+    (tmp_path / "r.cpp").write_text(PROG % part)
+    subprocess.run(["g++", "-std=c++17", "-o", str(tmp_path / "r"), str(tmp_path / "r.cpp")], check=True)
+    out = subprocess.run([str(tmp_path / "r")], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout
