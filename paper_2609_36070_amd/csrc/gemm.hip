@@ -21,10 +21,11 @@
 // copy of X or dY is ever written.  The shared expert runs through the same
 // kernel as one ungrouped problem of T rows.
 //
-// Pipeline: 256 x 256 block tile, K step 64, two LDS stages (2 x 64 KB)
-// filled by direct global->LDS loads (global_load_lds_dwordx4, no staging
-// registers): the next tile streams in while the current one is multiplied,
-// one fence-free barrier per K step.  8 waves as 2 (M) x 4 (N), 128 x 64 per
+// Pipeline: 256 x 256 block tile, K step 64, two LDS stages (2 x 64 KB; the
+// row products' own launches hold a third stage of B) filled by direct
+// global->LDS loads (global_load_lds_dwordx4, no staging registers): the next
+// tile streams in while the current one is multiplied, one fence-free barrier
+// per K step.  8 waves as 2 (M) x 4 (N), 128 x 64 per
 // wave (4 x 2 MFMA tiles).  Tiles are rastered XCD-aware.
 //
 // LDS tile formats:
@@ -150,6 +151,7 @@ __shared__ __attribute__((aligned(16))) uint16_t lds_a0[TILE_ELEMS];
 __shared__ __attribute__((aligned(16))) uint16_t lds_b0[TILE_ELEMS];
 __shared__ __attribute__((aligned(16))) uint16_t lds_a1[TILE_ELEMS];
 __shared__ __attribute__((aligned(16))) uint16_t lds_b1[TILE_ELEMS];
+__shared__ __attribute__((aligned(16))) uint16_t lds_b2[TILE_ELEMS];   // DEEP only
 __shared__ int s_info[2];
 // fused forward: first m-tile slot of every expert in the grouped raster
 // (entry E: the total), and the plan's offsets [E+1]
@@ -209,7 +211,8 @@ typedef int idx4_t __attribute__((ext_vector_type(4), aligned(4)));
 // evict operand panels that concurrently running tiles still share.
 DEV void st_nt(void *p, u32x4_t v) { __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t *>(p)); }
 
-template <int MODE, bool GROUPED, bool PERSISTENT = false>
+// DEEP: a third stage of B (row products in launches of their own).
+template <int MODE, bool GROUPED, bool PERSISTENT = false, bool DEEP = false>
 DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int *__restrict__ b_rows,
                    int vb, int nvb) {
     using Tr = Traits<MODE>;
@@ -253,6 +256,33 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
             ebase = uniform(s_offs[e]);
             row0 = ebase + (mt - uniform(s_tilebase[e])) * BM;
             row_end = uniform(s_offs[e + 1]);
+        } else if constexpr (GROUPED && DEEP) {
+            // every wave scans for itself: no LDS is left, and no barrier is needed
+            e = -1;
+            int within = 0, cum = 0;
+            for (int base = 0; base < g.E && e < 0; base += 64) {
+                const int ee = base + lane;
+                const int cnt = ee < g.E ? g.offsets[ee + 1] - g.offsets[ee] : 0;
+                const int tiles = cnt > 0 ? (cnt + BM - 1) / BM : 0;
+                int x = tiles;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const int y = __shfl_up(x, off, 64);
+                    if (lane >= off) x += y;
+                }
+                const int excl = cum + x - tiles;
+                const unsigned long long m = __ballot(mt >= excl && mt < excl + tiles);
+                if (m) {
+                    e = base + __builtin_ctzll(m);
+                    within = mt - __shfl(excl, __builtin_ctzll(m), 64);
+                }
+                cum += __shfl(x, 63, 64);
+            }
+            e = uniform(e);
+            if (e < 0) return;
+            ebase = uniform(g.offsets[e]);
+            row0 = ebase + uniform(within) * BM;
+            row_end = uniform(g.offsets[e + 1]);
         } else if constexpr (GROUPED) {
             if (tid == 0) s_info[0] = -1;
             __syncthreads();
@@ -648,7 +678,7 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
     // barrier stops the compiler from sinking them to their uses), so LDS
     // latency hides behind the matrix cores.
     //
-    // The next tile's direct loads (step nkt, into stages nla / nlb) go out in
+    // The next loads (A of step nkt into stage nla, B of step nktb into nlb) go out in
     // two halves, one operand ahead of the MFMAs of sub-step 0 and the other
     // ahead of sub-step 1, instead of all at the step's start: every wave of
     // every CU of an XCD reaches the step's barrier together, and 64 KB per CU
@@ -658,18 +688,22 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
     // The gathered WGRAD (index fetch and both operands as column tiles)
     // keeps all its loads at the step's start.
     constexpr int SPLIT = (MODE == WGRAD) ? 0 : (Tr::A_COL && !Tr::B_COL) ? 2 : 1;
-    auto compute = [&](const uint16_t *la, const uint16_t *lb, int nkt, uint16_t *nla, uint16_t *nlb) {
+    auto compute = [&](const uint16_t *la, const uint16_t *lb, int nkt, uint16_t *nla, int nktb,
+                       uint16_t *nlb) {
         bf16x8_t af[2][TM], bfr[2][TN];
         load_frags(la, lb, 0, af[0], bfr[0]);
 #pragma unroll
         for (int ks = 0; ks < BK / 16; ++ks) {
             const int cur = ks & 1;
             if (ks + 1 < BK / 16) load_frags(la, lb, ks + 1, af[cur ^ 1], bfr[cur ^ 1]);
-            if (SPLIT != 0 && nkt >= 0 && ks < 2) {
-                const int first = SPLIT == 1 ? LD_A : LD_B;
-                asm volatile("" ::: "memory");   // after this sub-step's LDS reads
-                issue(nkt, nla, nlb, ks == 0 ? (LD_IDX | first) : (LD_A | LD_B) ^ first);
-                asm volatile("" ::: "memory");
+            if (SPLIT != 0 && ks < 2) {
+                const int part = (ks == 0) == (SPLIT == 1) ? LD_A : LD_B;
+                const int step = part == LD_A ? nkt : nktb;
+                if (step >= 0) {
+                    asm volatile("" ::: "memory");   // after this sub-step's LDS reads
+                    issue(step, nla, nlb, ks == 0 ? (LD_IDX | part) : part);
+                    asm volatile("" ::: "memory");
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -681,32 +715,56 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
         }
     };
 
-    // Double-buffered K loop, unrolled by two so each half names its stages:
-    // wait for this wave's loads of the tile about to be read, barrier (all
-    // waves' loads landed, all reads of the other stage done), then compute on
-    // this stage while the next tile streams into the other one.
-    if (nk > 0) issue(0, lds_a0, lds_b0, LD_ALL);
     int kt = 0;
-    for (; kt + 1 < nk; kt += 2) {
-        wait_vmcnt<0>();
-        barrier_no_fence();
-        if constexpr (SPLIT == 0) {
-            issue(kt + 1, lds_a1, lds_b1, LD_ALL);
-            asm volatile("" ::: "memory");   // keep the loads ahead of this step's LDS reads
+    if constexpr (DEEP) {
+        // A one K step ahead, B two (its third stage takes the rest of LDS).
+        // With few rows per expert each weight byte comes from HBM for one or
+        // two m-tiles only, and one K step does not cover that round trip.
+        // Loads return in order, so leaving the LD_PER_OP issued last in
+        // flight (B of the step after the next) waits for everything before.
+        static_assert(SPLIT == 1 && !Tr::CMB && !Tr::WG && LD_PER_OP == 4, "A first, then B");
+        uint16_t *const sa[2] = {lds_a0, lds_a1}, *const sb[3] = {lds_b0, lds_b1, lds_b2};
+        if (nk > 0) issue(0, sa[0], sb[0], LD_ALL);
+        if (nk > 1) issue(1, nullptr, sb[1], LD_B);
+        for (; kt < nk; kt += 6) {
+#pragma unroll
+            for (int u = 0; u < 6; ++u) {
+                const int step = kt + u;
+                if (step >= nk) break;
+                if (step + 1 < nk) wait_vmcnt<LD_PER_OP>();
+                else wait_vmcnt<0>();
+                barrier_no_fence();
+                compute(sa[u & 1], sb[u % 3], step + 1 < nk ? step + 1 : -1, sa[(u + 1) & 1],
+                        step + 2 < nk ? step + 2 : -1, sb[(u + 2) % 3]);
+            }
         }
-        compute(lds_a0, lds_b0, kt + 1, lds_a1, lds_b1);
-        wait_vmcnt<0>();
-        barrier_no_fence();
-        if constexpr (SPLIT == 0) {
-            if (kt + 2 < nk) issue(kt + 2, lds_a0, lds_b0, LD_ALL);
-            asm volatile("" ::: "memory");
+    } else {
+        // Double-buffered K loop, unrolled by two so each half names its stages:
+        // wait for this wave's loads of the tile about to be read, barrier (all
+        // waves' loads landed, all reads of the other stage done), then compute on
+        // this stage while the next tile streams into the other one.
+        if (nk > 0) issue(0, lds_a0, lds_b0, LD_ALL);
+        for (; kt + 1 < nk; kt += 2) {
+            wait_vmcnt<0>();
+            barrier_no_fence();
+            if constexpr (SPLIT == 0) {
+                issue(kt + 1, lds_a1, lds_b1, LD_ALL);
+                asm volatile("" ::: "memory");   // keep the loads ahead of this step's LDS reads
+            }
+            compute(lds_a0, lds_b0, kt + 1, lds_a1, kt + 1, lds_b1);
+            wait_vmcnt<0>();
+            barrier_no_fence();
+            if constexpr (SPLIT == 0) {
+                if (kt + 2 < nk) issue(kt + 2, lds_a0, lds_b0, LD_ALL);
+                asm volatile("" ::: "memory");
+            }
+            compute(lds_a1, lds_b1, kt + 2 < nk ? kt + 2 : -1, lds_a0, kt + 2 < nk ? kt + 2 : -1, lds_b0);
         }
-        compute(lds_a1, lds_b1, kt + 2 < nk ? kt + 2 : -1, lds_a0, lds_b0);
-    }
-    if (kt < nk) {
-        wait_vmcnt<0>();
-        barrier_no_fence();
-        compute(lds_a0, lds_b0, -1, nullptr, nullptr);
+        if (kt < nk) {
+            wait_vmcnt<0>();
+            barrier_no_fence();
+            compute(lds_a0, lds_b0, -1, nullptr, -1, nullptr);
+        }
     }
     __syncthreads();
 
@@ -899,10 +957,10 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
     }
 }
 
-template <int MODE, bool GROUPED>
+template <int MODE, bool GROUPED, bool DEEP = false>
 __global__ __launch_bounds__(NTHREADS, 1) void gemm_kernel(GemmArgs g, const int *__restrict__ a_rows,
                                                           const int *__restrict__ b_rows) {
-    gemm_tile<MODE, GROUPED>(g, a_rows, b_rows, blockIdx.x, gridDim.x);
+    gemm_tile<MODE, GROUPED, false, DEEP>(g, a_rows, b_rows, blockIdx.x, gridDim.x);
 }
 
 // Several grouped weight-gradient products, optionally followed by one
@@ -937,16 +995,16 @@ __global__ __launch_bounds__(NTHREADS, 1) void gemm_batch_kernel(GemmBatch bt) {
         gemm_tile<WGRAD, true>(bt.g[i], bt.g[i].a_rows, bt.g[i].b_rows, vb, nvb);
 }
 
-template <int MODE>
+template <int MODE, bool DEEP = false>
 hipError_t launch_mode(GemmArgs g, int tiles_m, int ntn, hipStream_t st, long grid_blocks = 0) {
     const long tiles = (long)tiles_m * ntn;
     if (tiles <= 0) return hipSuccess;
     g.tiles_m = tiles_m;
     const unsigned grid = (unsigned)(grid_blocks > 0 ? grid_blocks : raster_grid(tiles_m, ntn));
     if (g.offsets)
-        gemm_kernel<MODE, true><<<dim3(grid), dim3(NTHREADS), 0, st>>>(g, g.a_rows, g.b_rows);
+        gemm_kernel<MODE, true, DEEP><<<dim3(grid), dim3(NTHREADS), 0, st>>>(g, g.a_rows, g.b_rows);
     else
-        gemm_kernel<MODE, false><<<dim3(grid), dim3(NTHREADS), 0, st>>>(g, g.a_rows, g.b_rows);
+        gemm_kernel<MODE, false, DEEP><<<dim3(grid), dim3(NTHREADS), 0, st>>>(g, g.a_rows, g.b_rows);
     return hipGetLastError();
 }
 
@@ -962,17 +1020,32 @@ static int mtiles(const GemmArgs &g, long rows, int groups) {
     return g.offsets ? (int)(rows / BM + (groups > 0 ? groups : 1)) : (int)((rows + BM - 1) / BM);
 }
 
+// The third stage of B pays while an expert's weights serve few m-tiles and
+// costs a little where they serve many (its loads then hit in L2 either way,
+// and more of them queue).  Forward, two / three stages (us), mean rows per
+// expert: 125: 394 / 369, 512 (128 experts): 906 / 878, 1000: 1315 / 1291,
+// 1024 (128 experts): 1570 / 1541, 2048: 2461 / 2453, 3000: 3580 / 3607, 4096:
+// 4752 / 4777.
+constexpr long DEEP_ROWS = 1024;
+
+template <int MODE>
+static hipError_t launch_rows(const GemmArgs &g, long rows, int groups, hipStream_t st) {
+    const int tm = mtiles(g, rows, groups), ntn = g.N / (MODE == FWD_UP ? BN / 2 : BN);
+    return rows <= DEEP_ROWS * (groups > 0 ? groups : 1) ? launch_mode<MODE, true>(g, tm, ntn, st)
+                                                        : launch_mode<MODE>(g, tm, ntn, st);
+}
+
 hipError_t launch_gemm_fwd_up(const GemmArgs &g, long rows, int groups, hipStream_t st) {
-    return launch_mode<FWD_UP>(g, mtiles(g, rows, groups), g.N / (BN / 2), st);
+    return launch_rows<FWD_UP>(g, rows, groups, st);
 }
 hipError_t launch_gemm_fwd_down(const GemmArgs &g, long rows, int groups, hipStream_t st) {
-    return launch_mode<FWD_DOWN>(g, mtiles(g, rows, groups), g.N / BN, st);
+    return launch_rows<FWD_DOWN>(g, rows, groups, st);
 }
 hipError_t launch_gemm_bwd_dgrad(const GemmArgs &g, long rows, int groups, hipStream_t st) {
-    return launch_mode<BWD_DGRAD>(g, mtiles(g, rows, groups), g.N / BN, st);
+    return launch_rows<BWD_DGRAD>(g, rows, groups, st);
 }
 hipError_t launch_gemm_bwd_dx(const GemmArgs &g, long rows, int groups, hipStream_t st) {
-    return launch_mode<BWD_DX>(g, mtiles(g, rows, groups), g.N / BN, st);
+    return launch_rows<BWD_DX>(g, rows, groups, st);
 }
 hipError_t launch_gemm_fwd_down_cmb(const GemmArgs &g, hipStream_t st) {
     if (g.offsets) return hipErrorInvalidValue;   // token tiles are not grouped
