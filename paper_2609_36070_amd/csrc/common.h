@@ -69,25 +69,36 @@ DEV u32x4_t pack_bf8(const f32x8 &v) {
                    pack_bf2(v[6], v[7])};
 }
 
-// XCD-aware raster of the grouped GEMMs.  Workgroups are dealt to the 8 XCDs
-// round-robin (workgroup b runs on XCD b % 8).  The tiles are ordered in
-// groups of RASTER_GM m-tiles x all n-tiles, walked m-tile fastest, and the
-// order is cut into chunks of RASTER_CHUNK = 32 tiles, about what an XCD runs
-// at once; chunk c goes to XCD c % 8.  A chunk shares RASTER_GM A panels and
-// ~8 B panels in its XCD's L2, and at any time the 8 XCDs work on 8
-// neighbouring chunks, which read the same expert's weights: those reads hit
-// in the Infinity Cache instead of each XCD streaming a different expert from
-// HBM (3-7 % faster than giving each XCD one contiguous run).  Dealing whole
-// groups instead left the XCDs uneven when there are few: 41 m-tiles x 12
-// n-tiles are 11 groups, so two XCDs ran three rounds while five ran one and
-// a half and the CUs were busy 58 % of the launch.  Whole forward, groups ->
-// chunks (us): 1000 tokens to 32 experts 580 -> 534; 4099 tokens to 8 experts
+// XCD-aware rasters.  Workgroups are dealt to the 8 XCDs round-robin
+// (workgroup b runs on XCD b % 8).  The N tiles of a launch are numbered so
+// that neighbours share operand panels, and the numbering is cut into chunks
+// of CH tiles, chunk c to XCD c % 8: a chunk shares its panels in that XCD's
+// L2, and at any time the 8 XCDs work on 8 neighbouring chunks, which read
+// the same expert's weights, so those reads hit in the Infinity Cache (3-7 %
+// faster than giving each XCD one contiguous run of tiles).  What is left
+// after the whole rounds of 8 chunks is dealt evenly, so no XCD runs more
+// tiles than ceil(N / (8 CH)) CH, and with CH = 32 no CU more than
+// ceil(N / 256).  -1: workgroup b has no tile.
+DEV int deal_tile(int b, int N, int CH) {
+    const int x = b % 8, j = b / 8, rounds = N / (8 * CH);
+    if (j < rounds * CH) return (j / CH * 8 + x) * CH + j % CH;
+    const int rest = N - rounds * 8 * CH, each = (rest + 7) / 8;
+    const int i = j - rounds * CH, t = x * each + i;
+    return i < each && t < rest ? rounds * 8 * CH + t : -1;
+}
+inline long deal_grid(long N, int CH) { return (N + 8 * CH - 1) / (8 * CH) * (8 * CH); }
+
+// Row products: groups of RASTER_GM m-tiles x all n-tiles, walked m-tile
+// fastest, in chunks of 32 tiles, what an XCD runs at once: 4 A panels and
+// ~8 B panels in its L2.  Dealing whole groups instead left the XCDs uneven
+// when there are few: 41 m-tiles x 12 n-tiles are 11 groups, so two XCDs ran
+// three rounds while five ran one and a half and the CUs were busy 58 % of
+// the launch.  Whole forward, groups -> chunks (us): 4099 tokens to 8 experts
 // and a shared one 4027 -> 3062 (the shared and the folded down product are
-// 17 m-tiles: 5 groups on 8 XCDs); 16384 tokens unchanged.  Slots past the
-// tiles return at once.
+// 17 m-tiles: 5 groups on 8 XCDs).
 constexpr int RASTER_GM = 4, RASTER_CHUNK = 32;
 
-// Place of tile number `group * RASTER_GM * ntn + within` of that order.
+// Place of tile `within` of group `group`.
 DEV bool map_group_tile(int group, int within, int tiles_m, int ntn, int &mt, int &nt) {
     const int first = group * RASTER_GM;
     if (first >= tiles_m) return false;
@@ -99,17 +110,13 @@ DEV bool map_group_tile(int group, int within, int tiles_m, int ntn, int &mt, in
 }
 
 DEV bool map_tile(int b, int tiles_m, int ntn, int &mt, int &nt) {
-    const int j = b / 8;
-    const int t = ((j / RASTER_CHUNK) * 8 + b % 8) * RASTER_CHUNK + j % RASTER_CHUNK;
+    const int t = deal_tile(b, tiles_m * ntn, RASTER_CHUNK);
     const int tpg = RASTER_GM * ntn;
-    return map_group_tile(t / tpg, t % tpg, tiles_m, ntn, mt, nt);
+    return t >= 0 && map_group_tile(t / tpg, t % tpg, tiles_m, ntn, mt, nt);
 }
 
-// Workgroups of a launch whose tiles map_tile places.
-inline long raster_grid(long tiles_m, int ntn) {
-    const long tiles = (tiles_m + RASTER_GM - 1) / RASTER_GM * RASTER_GM * ntn;
-    return (tiles + 8 * RASTER_CHUNK - 1) / (8 * RASTER_CHUNK) * (8 * RASTER_CHUNK);
-}
+// Workgroups of a launch whose tiles map_tile places (tiles_m or fewer m-tiles).
+inline long raster_grid(long tiles_m, int ntn) { return deal_grid(tiles_m * ntn, RASTER_CHUNK); }
 
 // The fused forward's raster: whole groups dealt to the XCDs, group g to XCD
 // g % 8, so that a tile and the tiles that wait for it can share an XCD.
@@ -123,37 +130,71 @@ inline long raster_grid_groups(long tiles_m, int ntn) {
     return 8 * ((groups + 7) / 8) * RASTER_GM * ntn;
 }
 
-// Weight-gradient raster.  A tile's cost is its expert's route count, so
-// XCDs that each ran whole experts would wait for the heaviest one (or idle
-// outright when a window of the bounded-memory backward holds only some of
-// the experts).  Instead each expert's ntm x ntn tiles are cut into blocks of
-// 4 x 4 tiles, the blocks of all experts are numbered expert by expert, and
-// block h goes to XCD h % 8: every XCD gets an equal share of each expert
-// (up to one block), and the 32 tiles an XCD runs at once are two such
-// blocks, each sharing 4 A and 4 B panels in that XCD's L2.
-// Grid: 8 * 16 * ceil(groups * blocks_per_expert / 8) workgroups.
-constexpr int WG_BM = 4, WG_BN = 4;
-__host__ __device__ __forceinline__ int wgrad_blocks_per_expert(int ntm, int ntn) {
-    return ((ntm + WG_BM - 1) / WG_BM) * ((ntn + WG_BN - 1) / WG_BN);
-}
+// Weight gradients: each expert's ntm x ntn tiles in column strips of 4
+// n-tiles (the last strip of what is left), walked n fastest, all experts in
+// one numbering, in chunks of 16 tiles: a 4 x 4 block sharing 4 A and 4 B
+// panels, or 8 x 2 in a strip of two.  A tile costs its expert's route count,
+// so an expert's chunks go to different XCDs.  (Numbering 4 x 4 blocks with
+// room for missing tiles gave some XCDs only partial blocks: at 16 x 6 tiles
+// per expert four XCDs ran 16 rounds and four ran 8.)
+constexpr int WG_STRIP = 4, WG_CHUNK = 16;
 DEV bool map_tile_wgrad(int b, int groups, int ntm, int ntn, int &cm, int &nt) {
-    constexpr int NX = 8, PER = WG_BM * WG_BN;
-    const int nbm = (ntm + WG_BM - 1) / WG_BM;
-    const int nb = wgrad_blocks_per_expert(ntm, ntn);
-    const int j = b / NX;                        // position in this XCD's sequence
-    const int h = (j / PER) * NX + b % NX;       // block
-    const int t = j % PER;                       // tile within the block, m fastest
-    const int e = h / nb, lb = h % nb;
-    if (e >= groups) return false;
-    const int mt = (lb % nbm) * WG_BM + t % WG_BM;
-    nt = (lb / nbm) * WG_BN + t / WG_BM;
-    if (mt >= ntm || nt >= ntn) return false;
-    cm = e * ntm + mt;
+    const int per = ntm * ntn;
+    const int t = deal_tile(b, groups * per, WG_CHUNK);
+    if (t < 0) return false;
+    const int e = t / per, i = t % per;
+    const int whole = ntn / WG_STRIP * WG_STRIP;       // n-tiles in strips of 4
+    const int strip = i < whole * ntm ? i / (WG_STRIP * ntm) : whole / WG_STRIP;
+    const int wid = i < whole * ntm ? WG_STRIP : ntn - whole;
+    const int w = i - strip * WG_STRIP * ntm;
+    cm = e * ntm + w / wid;
+    nt = strip * WG_STRIP + w % wid;
     return true;
 }
 
 // Workgroups of a launch whose tiles map_tile_wgrad places.
-inline long wgrad_grid(long groups, int ntm, int ntn) {
-    const long nblk = groups * wgrad_blocks_per_expert(ntm, ntn);
-    return 8L * WG_BM * WG_BN * ((nblk + 7) / 8);
+inline long wgrad_grid(long groups, int ntm, int ntn) { return deal_grid(groups * ntm * ntn, WG_CHUNK); }
+
+// The tile of workgroup b of a grouped row product over E <= 256 experts
+// (offsets: their plan rows) with BM-row m-tiles and ntn n-tiles: every wave
+// scans the experts' tile counts for itself (no LDS, no barrier), so the
+// raster deals the tiles there are, not the launch's upper bound.
+template <int BM>
+DEV bool place_tile(const int *__restrict__ offsets, int E, int b, int ntn, int lane, int &e,
+                    int &mt_in_e, int &slot, int &nt) {
+    int tiles[4], excl[4], cum = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int ee = 64 * q + lane;
+        const int cnt = ee < E ? offsets[ee + 1] - offsets[ee] : 0;
+        tiles[q] = cnt > 0 ? (cnt + BM - 1) / BM : 0;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        excl[q] = cum;
+        if (64 * q >= E) break;
+        int x = tiles[q];
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int y = __shfl_up(x, off, 64);
+            if (lane >= off) x += y;
+        }
+        excl[q] = cum + x - tiles[q];
+        cum += __shfl(x, 63, 64);
+    }
+    int mt = 0;
+    if (!map_tile(b, __builtin_amdgcn_readfirstlane(cum), ntn, mt, nt)) return false;
+    slot = mt;
+    e = -1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (64 * q >= E || e >= 0) break;
+        const unsigned long long m = __ballot(mt >= excl[q] && mt < excl[q] + tiles[q]);
+        if (m) {
+            e = 64 * q + __builtin_ctzll(m);
+            mt_in_e = __builtin_amdgcn_readfirstlane(mt - __shfl(excl[q], __builtin_ctzll(m), 64));
+        }
+    }
+    e = __builtin_amdgcn_readfirstlane(e);
+    return e >= 0;
 }

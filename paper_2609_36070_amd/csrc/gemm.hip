@@ -152,7 +152,6 @@ __shared__ __attribute__((aligned(16))) uint16_t lds_b0[TILE_ELEMS];
 __shared__ __attribute__((aligned(16))) uint16_t lds_a1[TILE_ELEMS];
 __shared__ __attribute__((aligned(16))) uint16_t lds_b1[TILE_ELEMS];
 __shared__ __attribute__((aligned(16))) uint16_t lds_b2[TILE_ELEMS];   // DEEP only
-__shared__ int s_info[2];
 // fused forward: first m-tile slot of every expert in the grouped raster
 // (entry E: the total), and the plan's offsets [E+1]
 __shared__ int s_tilebase[257];
@@ -236,9 +235,17 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
     if constexpr (Tr::GROUPED_ROWS) {
         const int ntn = (MODE == FWD_UP) ? g.N / (BN / 2) : g.N / BN;
         int mt = 0;
-        if (PERSISTENT ? !map_tile_groups(vb, g.tiles_m, ntn, mt, ntile)
-                       : !map_tile(vb, g.tiles_m, ntn, mt, ntile))
-            return;
+        if constexpr (PERSISTENT) {
+            if (!map_tile_groups(vb, g.tiles_m, ntn, mt, ntile)) return;
+        } else if constexpr (GROUPED) {
+            int within = 0;
+            if (!place_tile<BM>(g.offsets, g.E, vb, ntn, lane, e, within, mt, ntile)) return;
+            ebase = uniform(g.offsets[e]);
+            row0 = ebase + within * BM;
+            row_end = uniform(g.offsets[e + 1]);
+        } else {
+            if (!map_tile(vb, g.tiles_m, ntn, mt, ntile)) return;
+        }
         n0 = ntile * ((MODE == FWD_UP) ? BN / 2 : BN);
         if constexpr (GROUPED && PERSISTENT) {
             // the fused kernel keeps the grouped raster's prefix and the
@@ -256,63 +263,7 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
             ebase = uniform(s_offs[e]);
             row0 = ebase + (mt - uniform(s_tilebase[e])) * BM;
             row_end = uniform(s_offs[e + 1]);
-        } else if constexpr (GROUPED && DEEP) {
-            // every wave scans for itself: no LDS is left, and no barrier is needed
-            e = -1;
-            int within = 0, cum = 0;
-            for (int base = 0; base < g.E && e < 0; base += 64) {
-                const int ee = base + lane;
-                const int cnt = ee < g.E ? g.offsets[ee + 1] - g.offsets[ee] : 0;
-                const int tiles = cnt > 0 ? (cnt + BM - 1) / BM : 0;
-                int x = tiles;
-#pragma unroll
-                for (int off = 1; off < 64; off <<= 1) {
-                    const int y = __shfl_up(x, off, 64);
-                    if (lane >= off) x += y;
-                }
-                const int excl = cum + x - tiles;
-                const unsigned long long m = __ballot(mt >= excl && mt < excl + tiles);
-                if (m) {
-                    e = base + __builtin_ctzll(m);
-                    within = mt - __shfl(excl, __builtin_ctzll(m), 64);
-                }
-                cum += __shfl(x, 63, 64);
-            }
-            e = uniform(e);
-            if (e < 0) return;
-            ebase = uniform(g.offsets[e]);
-            row0 = ebase + uniform(within) * BM;
-            row_end = uniform(g.offsets[e + 1]);
-        } else if constexpr (GROUPED) {
-            if (tid == 0) s_info[0] = -1;
-            __syncthreads();
-            if (tid < 64) {
-                int cum = 0;
-                for (int base = 0; base < g.E; base += 64) {
-                    const int ee = base + lane;
-                    const int cnt = ee < g.E ? g.offsets[ee + 1] - g.offsets[ee] : 0;
-                    const int tiles = cnt > 0 ? (cnt + BM - 1) / BM : 0;
-                    int x = tiles;
-#pragma unroll
-                    for (int off = 1; off < 64; off <<= 1) {
-                        const int y = __shfl_up(x, off, 64);
-                        if (lane >= off) x += y;
-                    }
-                    const int excl = cum + x - tiles;
-                    if (ee < g.E && mt >= excl && mt < excl + tiles) {
-                        s_info[0] = ee;
-                        s_info[1] = mt - excl;
-                    }
-                    cum += __shfl(x, 63, 64);
-                }
-            }
-            __syncthreads();
-            e = uniform(s_info[0]);
-            if (e < 0) return;
-            ebase = uniform(g.offsets[e]);
-            row0 = ebase + uniform(s_info[1]) * BM;
-            row_end = uniform(g.offsets[e + 1]);
-        } else {
+        } else if constexpr (!GROUPED) {
             row0 = mt * BM;
             row_end = g.M;
             if (row0 >= row_end) return;

@@ -101,7 +101,6 @@ __global__ __launch_bounds__(NTHREADS, 1) void gemm_mx_kernel(MxGemmArgs g, cons
     __shared__ uint32_t sc_all[2 * BM + 2 * BN];
     uint32_t *const sc_a0 = sc_all, *const sc_a1 = sc_all + BM;
     uint32_t *const sc_b0 = sc_all + 2 * BM, *const sc_b1 = sc_all + 2 * BM + BN;
-    __shared__ int s_info[2];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -123,35 +122,10 @@ __global__ __launch_bounds__(NTHREADS, 1) void gemm_mx_kernel(MxGemmArgs g, cons
         nk_w = (uniform(g.offsets[e + 1]) - (int)kbase) / BK;
     } else {
         const int ntn = (MODE == MX_UP) ? g.N / (BN / 2) : g.N / BN;
-        int mt = 0;
-        if (!map_tile(blockIdx.x, g.tiles_m, ntn, mt, ntile)) return;
+        int slot = 0, within = 0;
+        if (!place_tile<BM>(g.offsets, g.E, blockIdx.x, ntn, lane, e, within, slot, ntile)) return;
         n0 = ntile * ((MODE == MX_UP) ? BN / 2 : BN);
-        if (tid == 0) s_info[0] = -1;
-        __syncthreads();
-        if (tid < 64) {
-            int cum = 0;
-            for (int base = 0; base < g.E; base += 64) {
-                const int ee = base + lane;
-                const int cnt = ee < g.E ? g.offsets[ee + 1] - g.offsets[ee] : 0;
-                const int tiles = cnt > 0 ? (cnt + BM - 1) / BM : 0;
-                int x = tiles;
-#pragma unroll
-                for (int off = 1; off < 64; off <<= 1) {
-                    const int y = __shfl_up(x, off, 64);
-                    if (lane >= off) x += y;
-                }
-                const int excl = cum + x - tiles;
-                if (ee < g.E && mt >= excl && mt < excl + tiles) {
-                    s_info[0] = ee;
-                    s_info[1] = mt - excl;
-                }
-                cum += __shfl(x, 63, 64);
-            }
-        }
-        __syncthreads();
-        e = uniform(s_info[0]);
-        if (e < 0) return;
-        row0 = uniform(g.offsets[e] + uniform(s_info[1]) * BM);
+        row0 = uniform(g.offsets[e]) + within * BM;
         row_end = uniform(g.offsets[e + 1]);
     }
     const long ks_row = g.K / 32;     // scale bytes per row

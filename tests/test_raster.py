@@ -34,13 +34,21 @@ int main() {
         for (int ntn : {1, 2, 3, 5, 8, 12, 16, 28, 56}) {
             if (walk(map_tile, raster_grid(tm, ntn), tm, ntn)) { std::printf("chunks %%d %%d\n", tm, ntn); ++bad; }
             if (walk(map_tile_groups, raster_grid_groups(tm, ntn), tm, ntn)) { std::printf("groups %%d %%d\n", tm, ntn); ++bad; }
-            // chunks: no XCD holds more than one chunk above another
-            int n[8] = {0};
-            for (long b = 0; b < raster_grid(tm, ntn); ++b) {
-                int mt, nt;
-                n[b %% 8] += map_tile((int)b, tm, ntn, mt, nt);
+            // a launch sized for more m-tiles than there are places the same tiles
+            if (walk(map_tile, raster_grid(tm + 37, ntn), tm, ntn)) { std::printf("larger grid %%d %%d\n", tm, ntn); ++bad; }
+            // no XCD runs more than its share of whole rounds
+            int n[8] = {0}, mt, nt;
+            for (long b = 0; b < raster_grid(tm, ntn); ++b) n[b %% 8] += map_tile((int)b, tm, ntn, mt, nt);
+            if (*std::max_element(n, n + 8) > (tm * ntn + 255) / 256 * 32) { std::printf("uneven %%d %%d\n", tm, ntn); ++bad; }
+            for (int groups : {1, 2, 3, 8, 32}) {
+                auto wg = [&](int b, int cmn, int ntn2, int &cm, int &nt2) {
+                    return map_tile_wgrad(b, groups, cmn / groups, ntn2, cm, nt2);
+                };
+                if (walk(wg, wgrad_grid(groups, tm, ntn), groups * tm, ntn)) { std::printf("wgrad %%d %%d %%d\n", groups, tm, ntn); ++bad; }
+                int w[8] = {0};
+                for (long b = 0; b < wgrad_grid(groups, tm, ntn); ++b) w[b %% 8] += wg((int)b, groups * tm, ntn, mt, nt);
+                if (*std::max_element(w, w + 8) > (groups * tm * ntn + 127) / 128 * 16) { std::printf("wgrad uneven %%d %%d %%d\n", groups, tm, ntn); ++bad; }
             }
-            if (*std::max_element(n, n + 8) - *std::min_element(n, n + 8) > RASTER_CHUNK) { std::printf("uneven %%d %%d\n", tm, ntn); ++bad; }
         }
     return bad;
 }
@@ -50,7 +58,7 @@ int main() {
 @pytest.mark.skipif(not shutil.which("g++"), reason="needs a host compiler")
 def test_every_tile_placed_once(tmp_path):
     src = open(os.path.join(CSRC, "common.h")).read()
-    part = src[src.index("constexpr int RASTER_GM"):src.index("// Weight-gradient raster.")]
+    part = src[src.index("// XCD-aware rasters."):src.index("// The tile of workgroup b of a grouped")]
     (tmp_path / "r.cpp").write_text(PROG % part)
     subprocess.run(["g++", "-std=c++17", "-o", str(tmp_path / "r"), str(tmp_path / "r.cpp")], check=True)
     out = subprocess.run([str(tmp_path / "r")], capture_output=True, text=True)
