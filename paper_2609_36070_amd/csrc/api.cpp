@@ -3,6 +3,7 @@
 // enqueued on the caller's stream and nothing here synchronises.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <cstring>
 #include <mutex>
@@ -41,6 +42,7 @@ struct Layout {
     size_t da32, db32, hw32;   // their fp32 sources dA, dB, w h (plan order)
     size_t mxw_total;
     long tpad;                 // their row pitch: the padded token positions' bound
+    int kslices;               // small batches: workgroups sharing an up/gate tile's K
     long act_rows;             // rows of the per-route activation buffers
     int dg_parts;
 };
@@ -81,9 +83,13 @@ Layout make_layout(const moe_shape &s, long ring_rows = -1) {
     L.Hs = take(T * fs * 2);
     L.Ysh = take(T * d * 2);
     // small batches with dense routing: the down products before their sum, fp32
-    const bool part = ring_rows < 0 && s.k == s.E && skinny_tiles((long)T, (long)R, (int)E) > 0;
-    L.part = take(part ? R * d * 4 : 0);
-    L.part_s = take(part && fs > 0 ? T * d * 4 : 0);
+    // and the up/gate products' K slices (the two are never live together)
+    const int tt = ring_rows < 0 ? skinny_tiles((long)T, (long)R, (int)E) : 0;
+    const bool part = tt > 0 && s.k == s.E;
+    L.kslices = tt > 0 ? skinny_kslices((long)T, (long)R, (int)E, (int)d, (int)f, (int)fs, tt) : 1;
+    const size_t upw = L.kslices > 1 ? 2 * (size_t)L.kslices : 0;
+    L.part = take(std::max(part ? R * d * 4 : 0, upw * R * f * 4));
+    L.part_s = take(std::max(part && fs > 0 ? T * d * 4 : 0, upw * T * fs * 4));
     L.fwd_total = o;
     L.dg_parts = (int)(f / (size_t)gemm_tile_n());
     L.dA = take(Ra * f * 2);
@@ -367,6 +373,8 @@ hipError_t small_forward(const moe_shape &sh, const Layout &L, void *ws, const m
     u.B = w->W_gate; u.B2 = w->W_up; u.ldb = f; u.b_estride = (long)d * f;
     u.C = at<uint16_t>(ws, L.H); u.ldc = f;
     u.row_w = dense ? topk_w : nullptr;
+    u.kslices = L.kslices;
+    u.Cf = at<float>(ws, L.part); u.Cfs = at<float>(ws, L.part_s);
     if (fs > 0) {
         u.As = X; u.lda_s = d; u.Ks = d; u.Ns = fs;
         u.Bs = w->Wg_s; u.Bs2 = w->Wu_s; u.ldb_s = fs;

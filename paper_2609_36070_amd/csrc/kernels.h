@@ -133,7 +133,7 @@ hipError_t launch_gemm_wgrad_batch(const GemmArgs *wg, int nw, int groups, const
 
 // Expert FFN products of small batches (skinny.hip): the routed experts' rows
 // of the plan and, when Ns > 0, the shared expert's T rows in one launch.
-enum SkinnyMode { SK_UP = 0, SK_DOWN = 1, SK_DOWN_PART = 2 };
+enum SkinnyMode { SK_UP = 0, SK_DOWN = 1, SK_DOWN_PART = 2, SK_UP_PART = 3 };
 struct SkinnyArgs {
     const uint16_t *A = nullptr;       // up: X by token; down: H by plan row
     long lda = 0;
@@ -153,10 +153,13 @@ struct SkinnyArgs {
     int Ks = 0, Ns = 0;
     uint16_t *Cs = nullptr;
     float *Cfs = nullptr;
-    int nshared = 0;                   // set by the launcher: workgroups of the shared expert
+    int kslices = 1;                   // up: workgroups sharing a tile's K; Cf [kslices][R][2 ldc] and
+                                       // Cfs [kslices][T][2 ldc_s] then hold their fp32 sums
+    int nshared = 0, ntiles = 0;       // set by the launcher: tiles of the shared expert, in all
 };
 // 16-row tiles per workgroup for T tokens and R routes, 0: not a small batch.
 int skinny_tiles(long T, long R, int E);
+int skinny_kslices(long T, long R, int E, int d, int f, int fs, int tt);
 hipError_t launch_skinny_up(const SkinnyArgs &g, int tt, hipStream_t st);
 hipError_t launch_skinny_down(const SkinnyArgs &g, int tt, hipStream_t st);
 // Dense routing: Y from the fp32 down products (part [R][d] by plan row, part_s [T][d] or null).

@@ -15,6 +15,9 @@
 // operand: product i takes column 8 r + i in row r.  The activations are the
 // column operand, 16 tokens each, from L2.
 //
+// Where the tiles are too few for the CUs, several workgroups share a tile's K
+// (skinny_kslices).
+//
 // The 4 partial sums are added through LDS in wave order, so results are
 // bitwise deterministic; then the SwiGLU, the row scale (dense routing) and
 // the stores.  The token of a plan row is perm[p] / k, so no plan-order
@@ -38,7 +41,7 @@ constexpr int SK_PITCH = SK_COLS + 4; // floats per token row of the reduction b
 
 template <int MODE, int TT>
 __global__ __launch_bounds__(64 * SK_NW, 2) void skinny_kernel(SkinnyArgs g) {
-    constexpr bool UP = MODE == SK_UP;
+    constexpr bool UP = MODE == SK_UP || MODE == SK_UP_PART;
     constexpr int NCOL = UP ? SK_COLS / 2 : SK_COLS;   // output columns per workgroup
     __shared__ __attribute__((aligned(16))) float red[SK_NW][16][SK_PITCH];
     constexpr int BM = 16 * TT;
@@ -47,7 +50,9 @@ __global__ __launch_bounds__(64 * SK_NW, 2) void skinny_kernel(SkinnyArgs g) {
     const int r = lane & 15, g4 = lane >> 4;
 
     // ---------------- which rows, which columns ----------------
-    const int b = blockIdx.x;
+    // with K split over several workgroups, slice `ks` of the tiles' K
+    const int ks = MODE == SK_UP_PART ? (int)(blockIdx.x / g.ntiles) : 0;
+    const int b = (int)blockIdx.x - ks * g.ntiles;
     const bool sh = b < g.nshared;    // the shared expert's tiles come first
     int e = 0, row0, row_end, ntile;
     if (sh) {
@@ -93,7 +98,10 @@ __global__ __launch_bounds__(64 * SK_NW, 2) void skinny_kernel(SkinnyArgs g) {
     const int n0 = ntile * NCOL;
 
     // ---------------- operand pointers of this lane ----------------
-    const int kw = 32 * wave + 8 * g4;                // its first k
+    // K in 256-row units over the slices
+    const int k0 = MODE == SK_UP_PART ? K / 256 * ks / g.kslices * 256 : 0;
+    const int k1 = MODE == SK_UP_PART ? K / 256 * (ks + 1) / g.kslices * 256 : K;
+    const int kw = k0 + 32 * wave + 8 * g4;           // its first k
     const uint16_t *wp;
     if constexpr (UP) {
         const uint16_t *m = r < 8 ? (sh ? g.Bs : g.B) : (sh ? g.Bs2 : g.B2);
@@ -150,7 +158,7 @@ __global__ __launch_bounds__(64 * SK_NW, 2) void skinny_kernel(SkinnyArgs g) {
         }
     };
 
-    const int steps = K / (32 * SK_NW);   // even: K is a multiple of 256
+    const int steps = (k1 - k0) / (32 * SK_NW);   // even: a multiple of 256 rows
     u32x4_t w[2][8], x[2][TT];
     load(w[0], x[0]);
     for (int s = 0; s < steps; s += 2) {
@@ -192,7 +200,13 @@ __global__ __launch_bounds__(64 * SK_NW, 2) void skinny_kernel(SkinnyArgs g) {
                 for (int q = 0; q < 4; ++q) v[q] = v[q] + u[q];
             }
             const int p = row0 + 16 * t + et;
-            if constexpr (UP) {
+            if constexpr (MODE == SK_UP_PART) {
+                // gate columns in the first half of a partial row, up in the second
+                const long f = sh ? g.ldc_s : g.ldc, rows = sh ? g.T : g.R;
+                if (p < row_end)
+                    *reinterpret_cast<f32x4_t *>((sh ? g.Cfs : g.Cf) + ((long)ks * rows + p) * 2 * f + n0
+                                                 + (en < NCOL ? en : f + en - NCOL)) = v;
+            } else if constexpr (UP) {
                 // the first half of a token's threads hold the gate, the second
                 // the up projection of the same f columns
                 f32x4_t u;
@@ -221,6 +235,37 @@ __global__ __launch_bounds__(64 * SK_NW, 2) void skinny_kernel(SkinnyArgs g) {
             }
         }
     }
+}
+
+// The K slices of a split up/gate product added in slice order, then the
+// SwiGLU: H for the plan's rows (blocks below `rblocks`) and the shared
+// expert's.  Four columns of one row per thread.
+__global__ __launch_bounds__(256) void skinny_act_kernel(SkinnyArgs g, long rblocks) {
+    const bool sh = blockIdx.x >= rblocks;
+    const long f = sh ? g.ldc_s : g.ldc, rows = sh ? g.T : g.R;
+    const long i = 4 * (((long)blockIdx.x - (sh ? rblocks : 0)) * 256 + threadIdx.x);
+    const long p = i / f, c = i % f;
+    if (p >= (sh ? rows : (long)g.offsets[g.E])) return;
+    const float *src = (sh ? g.Cfs : g.Cf) + p * 2 * f + c;
+    f32x4_t a = f32x4_t{0.f, 0.f, 0.f, 0.f}, b = a;
+    for (int s = 0; s < g.kslices; ++s) {
+        const f32x4_t u = *reinterpret_cast<const f32x4_t *>(src + s * rows * 2 * f);
+        const f32x4_t v = *reinterpret_cast<const f32x4_t *>(src + s * rows * 2 * f + f);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            a[q] = a[q] + u[q];
+            b[q] = b[q] + v[q];
+        }
+    }
+    float ws = 1.0f;
+    if (g.row_w && !sh) {
+        const int j = g.perm[p];
+        ws = (j >= 0 && j < g.R) ? g.row_w[j] : 0.f;
+    }
+    float h[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) h[q] = ws * (silu_f(a[q]) * b[q]);
+    *reinterpret_cast<u32x2_t *>((sh ? g.Cs : g.C) + i) = u32x2_t{pack_bf2(h[0], h[1]), pack_bf2(h[2], h[3])};
 }
 
 // Dense routing: Y[t] = sum over the experts' fp32 down products in ascending
@@ -256,10 +301,11 @@ __global__ __launch_bounds__(256) void dense_sum_kernel(const float *__restrict_
 
 template <int MODE>
 hipError_t launch_mode(SkinnyArgs g, int tt, hipStream_t st) {
-    const int ncols = MODE == SK_UP ? SK_COLS / 2 : SK_COLS, bm = 16 * tt;
+    const int ncols = MODE == SK_UP || MODE == SK_UP_PART ? SK_COLS / 2 : SK_COLS, bm = 16 * tt;
     const long slots = (g.R < g.E ? g.R : g.E) + g.R / bm;   // >= sum of ceil(rows / bm)
     g.nshared = g.Ns > 0 ? (g.T + bm - 1) / bm * (g.Ns / ncols) : 0;
-    const long grid = g.nshared + slots * (g.N / ncols);
+    g.ntiles = (int)(g.nshared + slots * (g.N / ncols));
+    const long grid = (long)g.ntiles * (MODE == SK_UP_PART ? g.kslices : 1);
     if (grid <= 0) return hipSuccess;
     const dim3 gr((unsigned)grid), bl(64 * SK_NW);
     if (tt == 1) skinny_kernel<MODE, 1><<<gr, bl, 0, st>>>(g);
@@ -280,8 +326,32 @@ int skinny_tiles(long T, long R, int E) {
     return R <= 64L * E ? 4 : 0;
 }
 
+// A CU's rate is bounded (its requests in flight), so a launch of one and a
+// bit workgroups per CU takes as long as two: 288 workgroups (8 experts and a
+// shared one of 2048 columns, d 7168) took 180 us at 61 tokens.  Below 640
+// workgroups (2.5 per CU) K is split over two or four, if each keeps 1024
+// rows, and the SwiGLU moves to a small launch: 137 + 8 us.  Whole forward at
+// 1 / 2 / 4 slices (us): 61 tokens 267 / 241 / 232, 1 token 212 / 195 / 182;
+// 32 experts, d 4096, 2 tokens 148 / 139 / 139.
+constexpr int SK_SPLIT_WGS = 640, SK_SPLIT_MAX = 4;
+
+int skinny_kslices(long T, long R, int E, int d, int f, int fs, int tt) {
+    const long bm = 16 * tt;
+    const long mt = (R < E ? R : E) > R / bm ? (R < E ? R : E) : R / bm;   // about the m-tiles there are
+    const long wgs = mt * (f / (SK_COLS / 2)) + (T + bm - 1) / bm * (fs / (SK_COLS / 2));
+    int s = 1;
+    while (s < SK_SPLIT_MAX && wgs * s < SK_SPLIT_WGS && d / (2 * s) >= 1024) s *= 2;
+    return s;
+}
+
 hipError_t launch_skinny_up(const SkinnyArgs &g, int tt, hipStream_t st) {
-    return launch_mode<SK_UP>(g, tt, st);
+    if (g.kslices <= 1) return launch_mode<SK_UP>(g, tt, st);
+    const hipError_t e = launch_mode<SK_UP_PART>(g, tt, st);
+    if (e != hipSuccess) return e;
+    const long rb = ((long)g.R * g.ldc / 4 + 255) / 256;
+    const long sb = g.Ns > 0 ? ((long)g.T * g.ldc_s / 4 + 255) / 256 : 0;
+    skinny_act_kernel<<<dim3((unsigned)(rb + sb)), dim3(256), 0, st>>>(g, rb);
+    return hipGetLastError();
 }
 hipError_t launch_skinny_down(const SkinnyArgs &g, int tt, hipStream_t st) {
     return g.Cf ? launch_mode<SK_DOWN_PART>(g, tt, st) : launch_mode<SK_DOWN>(g, tt, st);

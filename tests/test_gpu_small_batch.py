@@ -27,6 +27,9 @@ pytestmark = pytest.mark.gpu
     Workload("dense_65", T=65, d=512, E=5, k=5, f=512, f_s=256),      # past the bound: tile GEMMs
     Workload("dense_9", T=33, d=256, E=9, k=9, f=256),                # the sum over more than 8 experts
     Workload("skewed", T=250, d=256, E=16, k=4, f=256, bias_std=2.0),   # several 64-row tiles and empties
+    # K of the up/gate products over two (unequal) and four workgroups
+    Workload("split_2", T=5, d=2304, E=4, k=2, f=256, f_s=256, bias_std=0.5),
+    Workload("split_4_dense", T=40, d=4352, E=3, k=3, f=256, f_s=512),
     Workload("mean_64", T=128, d=256, E=4, k=2, f=512, f_s=512),      # R = 64 E exactly
 ], ids=lambda w: w.name)
 def test_small_batch_parity(w):
