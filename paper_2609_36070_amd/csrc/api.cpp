@@ -91,7 +91,7 @@ Layout make_layout(const moe_shape &s, long ring_rows = -1) {
     L.part = take(std::max(part ? R * d * 4 : 0, upw * R * f * 4));
     L.part_s = take(std::max(part && fs > 0 ? T * d * 4 : 0, upw * T * fs * 4));
     L.fwd_total = o;
-    L.dg_parts = (int)(f / (size_t)gemm_tile_n());
+    L.dg_parts = (int)(f / 128);   // BF16 dgrad: one per 128 columns (MXFP8: per 256)
     L.dA = take(Ra * f * 2);
     L.Hw = take(Ra * f * 2);
     L.dB = take(Ra * f * 2);
@@ -1428,14 +1428,14 @@ moe_status moe_backward_mx(const moe_shape *shape, const moe_bf16 *dY, const moe
         }
         g.E1 = at<float>(ws, L.a32); g.E2 = at<float>(ws, L.b32);
         g.rowscale = at<float>(ws, L.wperm);
-        g.dgpart = at<float>(ws, L.dgpart); g.dg_ld = L.dg_parts;
+        g.dgpart = at<float>(ws, L.dgpart); g.dg_ld = L.dg_parts / 2;
         g.a_bytes = (uint32_t)(Tn * d);
         g.as_bytes = (uint32_t)(Tn * d / 32);
         g.b_bytes = (uint32_t)((long)E * f * d);
         g.bs_bytes = (uint32_t)((long)E * f * d / 32);
         MOE_TRY(launch_gemm_mx_dgrad(g, R, E, s));
     }
-    MOE_TRY(launch_softmax_bwd(at<float>(ws, L.dgpart), L.dg_parts, plan->route_pos, topk_w, topk_idx,
+    MOE_TRY(launch_softmax_bwd(at<float>(ws, L.dgpart), L.dg_parts / 2, plan->route_pos, topk_w, topk_idx,
                                T, k, E, at<float>(ws, L.dg), dZ, s));
     {   // dXperm = Q(dA) Q(W_gate)^T + Q(dB) Q(W_up)^T
         MxGemmArgs g;

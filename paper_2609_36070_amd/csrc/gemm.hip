@@ -53,7 +53,7 @@ namespace {
 #ifndef MOE_GEMM_BK
 #define MOE_GEMM_BK 64
 #endif
-constexpr int BM = 256, BN = 256, BK = MOE_GEMM_BK;
+constexpr int TILE = 256, BM = TILE, BN = TILE, BK = MOE_GEMM_BK;
 static_assert(BK == 32 || BK == 64, "K step is 32 or 64");
 #ifndef MOE_GEMM_WAVES_M
 #define MOE_GEMM_WAVES_M 2
@@ -61,16 +61,17 @@ static_assert(BK == 32 || BK == 64, "K step is 32 or 64");
 #ifndef MOE_GEMM_WAVES_N
 #define MOE_GEMM_WAVES_N 4
 #endif
-constexpr int WAVES_M = MOE_GEMM_WAVES_M, WAVES_N = MOE_GEMM_WAVES_N;
-constexpr int NWAVES = WAVES_M * WAVES_N;
+constexpr int BIG_WAVES_M = MOE_GEMM_WAVES_M, BIG_WAVES_N = MOE_GEMM_WAVES_N;
+constexpr int NWAVES = BIG_WAVES_M * BIG_WAVES_N;
 constexpr int NTHREADS = 64 * NWAVES;
-constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-constexpr int TM = WM / 32, TN = WN / 32;
-constexpr int TILE_ELEMS = BM * BK;        // per operand per stage (bf16 elements)
+constexpr int TILE_ELEMS = BM * BK;        // bf16 elements of one 32 KB stage array
 constexpr int ROWS_PER_LD = 512 / BK;      // row-tile rows covered by one 1 KB wave load
-constexpr int LD_PER_OP = (BK / 2) / NWAVES;  // 1 KB direct loads per operand per wave per K step
-constexpr int LOADS_PER_K = 2 * LD_PER_OP; // direct-load instructions per thread per K step
-static_assert(WN == 64 || WN == 128, "gate/up column pairs and the epilogue need 64- or 128-column wave tiles");
+
+// How a workgroup runs its tile.  BASE: 256 x 256, two stages, each operand's
+// tile an array of its own.  DEEP: the same with a third stage of B.
+// QUARTER: one 128 x 128 quarter of a tile of the launch's last, partial round,
+// four stages with both operands' tiles in one array each.
+enum Shape { BASE = 0, DEEP = 1, QUARTER = 2 };
 
 enum Mode { FWD_UP = 0, FWD_DOWN = 1, BWD_DGRAD = 2, BWD_DX = 3, WGRAD = 4, FWD_DOWN_CMB = 5,
             BWD_DX_CMB = 6, WGRAD_T = 7, WGRAD_TB = 8 };
@@ -126,6 +127,7 @@ DEV bf16x8_t frag_row(const uint16_t *t, int r0, int ks, int lane) {
 // Fragment for MFMA operand columns [n0, n0+32) from a col tile, k step ks.
 // Lane l gets column n0 + (l & 31) at k = 16 ks + 8 (l >> 5) + 0..7, built
 // from two transposing reads of 4 k rows each.
+template <int BN>
 DEV bf16x8_t frag_col(const uint16_t *t, int n0, int ks, int lane) {
     const int i = lane & 15, grp = lane >> 4;
     const int n = n0 + 16 * (grp & 1) + 4 * (i & 3);
@@ -151,14 +153,12 @@ __shared__ __attribute__((aligned(16))) uint16_t lds_a0[TILE_ELEMS];
 __shared__ __attribute__((aligned(16))) uint16_t lds_b0[TILE_ELEMS];
 __shared__ __attribute__((aligned(16))) uint16_t lds_a1[TILE_ELEMS];
 __shared__ __attribute__((aligned(16))) uint16_t lds_b1[TILE_ELEMS];
-__shared__ __attribute__((aligned(16))) uint16_t lds_b2[TILE_ELEMS];   // DEEP only
+__shared__ __attribute__((aligned(16))) uint16_t lds_b2[TILE_ELEMS];   // the DEEP shape only
 // fused forward: first m-tile slot of every expert in the grouped raster
 // (entry E: the total), and the plan's offsets [E+1]
 __shared__ int s_tilebase[257];
 __shared__ int s_offs[257];
 
-// One output tile of product MODE: workgroup vb of a grid of nvb (a multiple
-// of 8, so vb % 8 is the XCD the tile runs on).
 // Fused forward: the longest a workgroup waits for a counter, in ticks of
 // the 100 MHz real-time clock (0.2 s; a legitimate wait lasts a few tile
 // times, well under 10 ms).  A wait that runs out sets bit 1 of the error
@@ -210,10 +210,63 @@ typedef int idx4_t __attribute__((ext_vector_type(4), aligned(4)));
 // evict operand panels that concurrently running tiles still share.
 DEV void st_nt(void *p, u32x4_t v) { __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t *>(p)); }
 
-// DEEP: a third stage of B (row products in launches of their own).
-template <int MODE, bool GROUPED, bool PERSISTENT = false, bool DEEP = false>
+// Where a row product's tile sits: expert, its first plan row, the tile's first
+// row and the end of its region, first (f) column, n-tile, m-tile slot.
+struct TilePos {
+    int e, ebase, row0, row_end, n0, ntile, slot;
+};
+
+// The tile of workgroup vb of a row product in a launch of its own, and its
+// shape (-1: none).  With `split` the tiles of a short last round are dealt as
+// quarters (deal_tile_split).
+template <int MODE, bool GROUPED>
+DEV int place_row_tile(const GemmArgs &g, int vb, bool split, TilePos &t) {
+    constexpr int NC = MODE == FWD_UP ? BN / 2 : BN;   // columns per tile
+    const int lane = threadIdx.x & 63, ntn = g.N / NC;
+    int tiles_m, quarter = -1, mt = 0, within = 0;
+    ExpertTiles<BM> x;
+    if constexpr (GROUPED) {
+        x.scan(g.offsets, g.E, lane);
+        tiles_m = x.total;
+    } else {
+        tiles_m = (g.M + BM - 1) / BM;
+    }
+    const int n = tiles_m * ntn;
+    const int i = split ? deal_tile_split(vb, n, quarter) : deal_tile(vb, n, RASTER_CHUNK);
+    if (i < 0 || !map_group_tile(i / (RASTER_GM * ntn), i % (RASTER_GM * ntn), tiles_m, ntn, mt, t.ntile))
+        return -1;
+    t.slot = mt;
+    if constexpr (GROUPED) {
+        t.e = x.find(mt, within);
+        t.ebase = uniform(g.offsets[t.e]);
+        t.row0 = t.ebase + within * BM;
+        t.row_end = uniform(g.offsets[t.e + 1]);
+    } else {
+        t.e = t.ebase = 0;
+        t.row0 = mt * BM;
+        t.row_end = g.M;
+    }
+    t.n0 = t.ntile * NC;
+    if (quarter < 0) return BASE;
+    t.row0 += (quarter & 1) * (BM / 2);
+    t.n0 += (quarter >> 1) * (NC / 2);
+    return t.row0 < t.row_end ? QUARTER : -1;
+}
+
+// One output tile of product MODE.  Row products of their own launches come
+// with their place; weight gradients and the persistent forward find it from
+// workgroup vb of a grid of nvb (a multiple of 8, so vb % 8 is the XCD the
+// tile runs on).
+template <int MODE, bool GROUPED, bool PERSISTENT = false, int SHAPE = BASE>
 DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int *__restrict__ b_rows,
-                   int vb, int nvb) {
+                   int vb, int nvb, const TilePos &pos = TilePos{}) {
+    constexpr int BM = SHAPE == QUARTER ? TILE / 2 : TILE, BN = BM;
+    constexpr int WAVES_M = SHAPE == QUARTER ? 4 : BIG_WAVES_M, WAVES_N = NWAVES / WAVES_M;
+    constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
+    static_assert(WN == 64 || WN == 128, "gate/up column pairs and the epilogue need 64- or 128-column wave tiles");
+    constexpr int LD_PER_OP = BM * BK / 512 / NWAVES;   // 1 KB direct loads per operand per wave per K step
+    constexpr int KR_PER_LD = 512 / BN;                 // col-tile k rows covered by one of them
+    constexpr int LANES_PER_KR = 64 / KR_PER_LD;
     using Tr = Traits<MODE>;
     int slot = 0;   // m-tile slot of a row product (fused forward dependencies)
 
@@ -235,38 +288,35 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
     if constexpr (Tr::GROUPED_ROWS) {
         const int ntn = (MODE == FWD_UP) ? g.N / (BN / 2) : g.N / BN;
         int mt = 0;
-        if constexpr (PERSISTENT) {
-            if (!map_tile_groups(vb, g.tiles_m, ntn, mt, ntile)) return;
-        } else if constexpr (GROUPED) {
-            int within = 0;
-            if (!place_tile<BM>(g.offsets, g.E, vb, ntn, lane, e, within, mt, ntile)) return;
-            ebase = uniform(g.offsets[e]);
-            row0 = ebase + within * BM;
-            row_end = uniform(g.offsets[e + 1]);
+        if constexpr (!PERSISTENT) {
+            e = pos.e; ebase = pos.ebase;
+            row0 = pos.row0; row_end = pos.row_end;
+            n0 = pos.n0; ntile = pos.ntile;
+            mt = pos.slot;
         } else {
-            if (!map_tile(vb, g.tiles_m, ntn, mt, ntile)) return;
-        }
-        n0 = ntile * ((MODE == FWD_UP) ? BN / 2 : BN);
-        if constexpr (GROUPED && PERSISTENT) {
-            // the fused kernel keeps the grouped raster's prefix and the
-            // offsets in LDS: each wave finds the expert of m-tile slot mt by
-            // a ballot over them (no global loads, no barrier)
-            e = -1;
-            for (int base = 0; base < g.E && e < 0; base += 64) {
-                const int ee = base + lane;
-                const bool hit = ee < g.E && mt >= s_tilebase[ee] && mt < s_tilebase[ee + 1];
-                const unsigned long long m = __ballot(hit);
-                if (m) e = base + __builtin_ctzll(m);
+            if (!map_tile_groups(vb, g.tiles_m, ntn, mt, ntile)) return;
+            n0 = ntile * ((MODE == FWD_UP) ? BN / 2 : BN);
+            if constexpr (GROUPED) {
+                // the fused kernel keeps the grouped raster's prefix and the
+                // offsets in LDS: each wave finds the expert of m-tile slot mt by
+                // a ballot over them (no global loads, no barrier)
+                e = -1;
+                for (int base = 0; base < g.E && e < 0; base += 64) {
+                    const int ee = base + lane;
+                    const bool hit = ee < g.E && mt >= s_tilebase[ee] && mt < s_tilebase[ee + 1];
+                    const unsigned long long m = __ballot(hit);
+                    if (m) e = base + __builtin_ctzll(m);
+                }
+                e = uniform(e);
+                if (e < 0) return;
+                ebase = uniform(s_offs[e]);
+                row0 = ebase + (mt - uniform(s_tilebase[e])) * BM;
+                row_end = uniform(s_offs[e + 1]);
+            } else {
+                row0 = mt * BM;
+                row_end = g.M;
+                if (row0 >= row_end) return;
             }
-            e = uniform(e);
-            if (e < 0) return;
-            ebase = uniform(s_offs[e]);
-            row0 = ebase + (mt - uniform(s_tilebase[e])) * BM;
-            row_end = uniform(s_offs[e + 1]);
-        } else if constexpr (!GROUPED) {
-            row0 = mt * BM;
-            row_end = g.M;
-            if (row0 >= row_end) return;
         }
         klen = g.K;
         slot = mt;
@@ -307,8 +357,8 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
     // of the stage's tile.
     //   row tile: instruction q covers rows 8 q .. 8 q + 7; lane -> row
     //             8 q + lane / 8, physical 16-byte chunk lane & 7.
-    //   col tile: instruction q covers k rows 2 q, 2 q + 1; lane -> k row
-    //             2 q + lane / 32, physical 16-byte slot lane & 31.
+    //   col tile: instruction q covers k rows 2 q, 2 q + 1 (four in a quarter);
+    //             lane -> k row 2 q + lane / 32, physical 16-byte slot lane & 31.
     const uint16_t *a_row[LD_PER_OP];   // row tile: row base (+ chunk), K offset added per step
     const uint16_t *a2_row[LD_PER_OP];
     const uint16_t *b_row[LD_PER_OP];
@@ -379,7 +429,7 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
 
     // column (within the 256-wide tile) that this lane's 16-byte col-tile load covers
     auto col_of = [&](int kr) {
-        const int slot = lane & 31;
+        const int slot = lane % LANES_PER_KR;
         const int b = col_swz(kr, slot >> 1);       // logical 32-byte block
         return 16 * b + 8 * (slot & 1);
     };
@@ -401,7 +451,7 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
             cm_c[i] = 8u * (uint32_t)row_swz(r, lane % (BK / 8));
             if constexpr (Tr::B_COL) {
                 // the routed and shared down weights share the row pitch d
-                const int kr = 2 * (LD_PER_OP * wave + i) + (lane >> 5);
+                const int kr = KR_PER_LD * (LD_PER_OP * wave + i) + lane / LANES_PER_KR;
                 cm_b[i] = (uint32_t)(kr * g.ldb + n0 + col_of(kr));
             } else {
                 cm_b[i] = (uint32_t)(n0 + r);
@@ -460,7 +510,7 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
     if constexpr (MODE == FWD_UP || MODE == FWD_DOWN) {
 #pragma unroll
         for (int i = 0; i < LD_PER_OP; ++i) {
-            const int kr = 2 * (LD_PER_OP * wave + i) + (lane >> 5);
+            const int kr = KR_PER_LD * (LD_PER_OP * wave + i) + lane / LANES_PER_KR;
             const int col = col_of(kr);
             if constexpr (MODE == FWD_UP) {
                 // tile columns: 32-column groups alternate gate / up over the same f range
@@ -556,7 +606,7 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
         } else {
 #pragma unroll
             for (int i = 0; i < LD_PER_OP; ++i) {
-                const int kr = 2 * (LD_PER_OP * wave + i) + (lane >> 5);
+                const int kr = KR_PER_LD * (LD_PER_OP * wave + i) + lane / LANES_PER_KR;
                 const int kk = kt * BK + kr;
                 const int col = col_of(kr);
                 const uint16_t *src = kk < klen ? g.A + (long)pa[i] * g.lda + a_col_off + col
@@ -575,7 +625,7 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
         } else {
 #pragma unroll
             for (int i = 0; i < LD_PER_OP; ++i) {
-                const int kr = 2 * (LD_PER_OP * wave + i) + (lane >> 5);
+                const int kr = KR_PER_LD * (LD_PER_OP * wave + i) + lane / LANES_PER_KR;
                 const int kk = kt * BK + kr;
                 const int col = col_of(kr);
                 const uint16_t *src;
@@ -615,12 +665,12 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
                           bf16x8_t (&bfr)[TN]) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            if constexpr (Tr::A_COL) af[i] = frag_col(la, wm * WM + 32 * i, ks, lane);
+            if constexpr (Tr::A_COL) af[i] = frag_col<BN>(la, wm * WM + 32 * i, ks, lane);
             else af[i] = frag_row(la, wm * WM + 32 * i, ks, lane);
         }
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-            if constexpr (Tr::B_COL) bfr[j] = frag_col(lb, wn * WN + 32 * j, ks, lane);
+            if constexpr (Tr::B_COL) bfr[j] = frag_col<BN>(lb, wn * WN + 32 * j, ks, lane);
             else bfr[j] = frag_row(lb, wn * WN + 32 * j, ks, lane);
         }
     };
@@ -667,7 +717,32 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
     };
 
     int kt = 0;
-    if constexpr (DEEP) {
+    if constexpr (SHAPE == QUARTER) {
+        // Four stages, three K steps in flight: a step waits for its own
+        // loads (in order, so the later steps' stay in flight), then the
+        // barrier frees the stage that was read in the step before.
+        uint16_t *const stg[4] = {lds_a0, lds_b0, lds_a1, lds_b1};
+        constexpr int HALF = BM * BK, LPK = 2 * LD_PER_OP;
+        static_assert(2 * HALF <= TILE_ELEMS, "both operands in one array");
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (i < nk) issue(i, stg[i], stg[i] + HALF, LD_ALL);
+        for (; kt < nk; kt += 4) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int step = kt + u;
+                if (step >= nk) break;
+                const int later = nk - 1 - step;
+                if (later >= 2) wait_vmcnt<2 * LPK>();
+                else if (later == 1) wait_vmcnt<LPK>();
+                else wait_vmcnt<0>();
+                barrier_no_fence();
+                if (step + 3 < nk) issue(step + 3, stg[(u + 3) & 3], stg[(u + 3) & 3] + HALF, LD_ALL);
+                asm volatile("" ::: "memory");
+                compute(stg[u], stg[u] + HALF, -1, nullptr, -1, nullptr);
+            }
+        }
+    } else if constexpr (SHAPE == DEEP) {
         // A one K step ahead, B two (its third stage takes the rest of LDS).
         // With few rows per expert each weight byte comes from HBM for one or
         // two m-tiles only, and one K step does not cover that round trip.
@@ -866,10 +941,15 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
         if (g.dgpart && tid < BM) {
             const int p = row0 + tid;
             if (p < row_end) {
-                float sum = red[tid];
+                // one partial per 128 columns, whichever shape computed them
+                constexpr int WP = 128 / WN;
 #pragma unroll
-                for (int w = 1; w < WAVES_N; ++w) sum = sum + red[w * BM + tid];
-                g.dgpart[(long)p * g.dg_ld + ntile] = sum;
+                for (int h = 0; h < BN / 128; ++h) {
+                    float sum = red[h * WP * BM + tid];
+#pragma unroll
+                    for (int w = 1; w < WP; ++w) sum = sum + red[(h * WP + w) * BM + tid];
+                    g.dgpart[(long)p * g.dg_ld + n0 / 128 + h] = sum;
+                }
             }
         }
     } else {  // WGRAD, WGRAD_T, WGRAD_TB
@@ -908,10 +988,24 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
     }
 }
 
-template <int MODE, bool GROUPED, bool DEEP = false>
+template <int MODE, bool GROUPED, int SHAPE = BASE>
 __global__ __launch_bounds__(NTHREADS, 1) void gemm_kernel(GemmArgs g, const int *__restrict__ a_rows,
                                                           const int *__restrict__ b_rows) {
-    gemm_tile<MODE, GROUPED, false, DEEP>(g, a_rows, b_rows, blockIdx.x, gridDim.x);
+    if constexpr (Traits<MODE>::GROUPED_ROWS) {
+        constexpr bool SPLIT = !Traits<MODE>::CMB;
+        TilePos t;
+        const int shape = place_row_tile<MODE, GROUPED>(g, blockIdx.x, SPLIT, t);
+        if (shape < 0) return;
+        if constexpr (SPLIT) {
+            if (shape == QUARTER) {
+                gemm_tile<MODE, GROUPED, false, QUARTER>(g, a_rows, b_rows, 0, 0, t);
+                return;
+            }
+        }
+        gemm_tile<MODE, GROUPED, false, SHAPE>(g, a_rows, b_rows, 0, 0, t);
+    } else {
+        gemm_tile<MODE, GROUPED>(g, a_rows, b_rows, blockIdx.x, gridDim.x);
+    }
 }
 
 // Several grouped weight-gradient products, optionally followed by one
@@ -936,9 +1030,11 @@ __global__ __launch_bounds__(NTHREADS, 1) void gemm_batch_kernel(GemmBatch bt) {
     for (int j = 1; j < MAX_BATCH; ++j)
         if (j < bt.n && b >= bt.start[j]) i = j;
     const int vb = b - bt.start[i], nvb = bt.start[i + 1] - bt.start[i];
-    if (bt.up_last && i == bt.n - 1)
-        gemm_tile<FWD_UP, true>(bt.g[i], bt.g[i].a_rows, bt.g[i].b_rows, vb, nvb);
-    else if (bt.mode[i] == 1)
+    if (bt.up_last && i == bt.n - 1) {
+        TilePos t;
+        if (place_row_tile<FWD_UP, true>(bt.g[i], vb, false, t) < 0) return;
+        gemm_tile<FWD_UP, true>(bt.g[i], bt.g[i].a_rows, bt.g[i].b_rows, vb, nvb, t);
+    } else if (bt.mode[i] == 1)
         gemm_tile<WGRAD_T, true>(bt.g[i], bt.g[i].a_rows, bt.g[i].b_rows, vb, nvb);
     else if (bt.mode[i] == 2)
         gemm_tile<WGRAD_TB, true>(bt.g[i], bt.g[i].a_rows, bt.g[i].b_rows, vb, nvb);
@@ -946,23 +1042,22 @@ __global__ __launch_bounds__(NTHREADS, 1) void gemm_batch_kernel(GemmBatch bt) {
         gemm_tile<WGRAD, true>(bt.g[i], bt.g[i].a_rows, bt.g[i].b_rows, vb, nvb);
 }
 
-template <int MODE, bool DEEP = false>
+template <int MODE, int SHAPE = BASE>
 hipError_t launch_mode(GemmArgs g, int tiles_m, int ntn, hipStream_t st, long grid_blocks = 0) {
     const long tiles = (long)tiles_m * ntn;
     if (tiles <= 0) return hipSuccess;
     g.tiles_m = tiles_m;
-    const unsigned grid = (unsigned)(grid_blocks > 0 ? grid_blocks : raster_grid(tiles_m, ntn));
+    const unsigned grid = (unsigned)(grid_blocks > 0 ? grid_blocks : split_grid(tiles_m, ntn));
     if (g.offsets)
-        gemm_kernel<MODE, true, DEEP><<<dim3(grid), dim3(NTHREADS), 0, st>>>(g, g.a_rows, g.b_rows);
+        gemm_kernel<MODE, true, SHAPE><<<dim3(grid), dim3(NTHREADS), 0, st>>>(g, g.a_rows, g.b_rows);
     else
-        gemm_kernel<MODE, false, DEEP><<<dim3(grid), dim3(NTHREADS), 0, st>>>(g, g.a_rows, g.b_rows);
+        gemm_kernel<MODE, false, SHAPE><<<dim3(grid), dim3(NTHREADS), 0, st>>>(g, g.a_rows, g.b_rows);
     return hipGetLastError();
 }
 
 }  // namespace
 
 int gemm_tile_m() { return BM; }
-int gemm_tile_n() { return BN; }
 
 // m-tile slots of a row problem.  Grouped: an upper bound on
 // sum_e ceil(M_e / BM), which is at most rows / BM + groups; slots past the
@@ -982,7 +1077,7 @@ constexpr long DEEP_ROWS = 1024;
 template <int MODE>
 static hipError_t launch_rows(const GemmArgs &g, long rows, int groups, hipStream_t st) {
     const int tm = mtiles(g, rows, groups), ntn = g.N / (MODE == FWD_UP ? BN / 2 : BN);
-    return rows <= DEEP_ROWS * (groups > 0 ? groups : 1) ? launch_mode<MODE, true>(g, tm, ntn, st)
+    return rows <= DEEP_ROWS * (groups > 0 ? groups : 1) ? launch_mode<MODE, DEEP>(g, tm, ntn, st)
                                                         : launch_mode<MODE>(g, tm, ntn, st);
 }
 

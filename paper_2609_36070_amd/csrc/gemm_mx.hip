@@ -122,8 +122,8 @@ __global__ __launch_bounds__(NTHREADS, 1) void gemm_mx_kernel(MxGemmArgs g, cons
         nk_w = (uniform(g.offsets[e + 1]) - (int)kbase) / BK;
     } else {
         const int ntn = (MODE == MX_UP) ? g.N / (BN / 2) : g.N / BN;
-        int slot = 0, within = 0;
-        if (!place_tile<BM>(g.offsets, g.E, blockIdx.x, ntn, lane, e, within, slot, ntile)) return;
+        int within = 0;
+        if (!place_tile<BM>(g.offsets, g.E, blockIdx.x, ntn, lane, e, within, ntile)) return;
         n0 = ntile * ((MODE == MX_UP) ? BN / 2 : BN);
         row0 = uniform(g.offsets[e]) + within * BM;
         row_end = uniform(g.offsets[e + 1]);

@@ -83,7 +83,6 @@ struct GemmArgs {
 };
 
 int gemm_tile_m();
-int gemm_tile_n();
 hipError_t launch_gemm_fwd_up(const GemmArgs &g, long rows, int groups, hipStream_t st);
 hipError_t launch_gemm_fwd_down(const GemmArgs &g, long rows, int groups, hipStream_t st);
 hipError_t launch_gemm_bwd_dgrad(const GemmArgs &g, long rows, int groups, hipStream_t st);

@@ -40,6 +40,17 @@ int main() {
             int n[8] = {0}, mt, nt;
             for (long b = 0; b < raster_grid(tm, ntn); ++b) n[b %% 8] += map_tile((int)b, tm, ntn, mt, nt);
             if (*std::max_element(n, n + 8) > (tm * ntn + 255) / 256 * 32) { std::printf("uneven %%d %%d\n", tm, ntn); ++bad; }
+            // with a short last round split: every tile once, whole or in its four quarters
+            std::set<std::pair<int, int>> seen;
+            long whole = 0;
+            for (long b = 0; b < split_grid(tm, ntn); ++b) {
+                int q;
+                const int t = deal_tile_split((int)b, tm * ntn, q);
+                if (t < 0) continue;
+                if (t >= tm * ntn || q > 3 || !seen.insert({t, q}).second) { std::printf("split %%d %%d\n", tm, ntn); ++bad; }
+                whole += q < 0 ? 4 : 1;
+            }
+            if (whole != 4L * tm * ntn) { std::printf("split misses %%d %%d\n", tm, ntn); ++bad; }
             for (int groups : {1, 2, 3, 8, 32}) {
                 auto wg = [&](int b, int cmn, int ntn2, int &cm, int &nt2) {
                     return map_tile_wgrad(b, groups, cmn / groups, ntn2, cm, nt2);
@@ -58,7 +69,7 @@ int main() {
 @pytest.mark.skipif(not shutil.which("g++"), reason="needs a host compiler")
 def test_every_tile_placed_once(tmp_path):
     src = open(os.path.join(CSRC, "common.h")).read()
-    part = src[src.index("// XCD-aware rasters."):src.index("// The tile of workgroup b of a grouped")]
+    part = src[src.index("// XCD-aware rasters."):src.index("// The BM-row m-tiles of E <= 256")]
     (tmp_path / "r.cpp").write_text(PROG % part)
     subprocess.run(["g++", "-std=c++17", "-o", str(tmp_path / "r"), str(tmp_path / "r.cpp")], check=True)
     out = subprocess.run([str(tmp_path / "r")], capture_output=True, text=True)
