@@ -161,16 +161,24 @@ def _p(t):
         return None
     if isinstance(t, int):
         return t
-    if t.numel() == 0:
-        # torch reports NULL for empty tensors; pass the (non-empty) storage instead
-        return t.untyped_storage().data_ptr()
-    return t.data_ptr()
+    # torch reports NULL for empty tensors; pass the (non-empty) storage instead
+    return t.data_ptr() or t.untyped_storage().data_ptr()
+
+
+# torch's current stream as the raw handle, without the Stream object that
+# torch.cuda.current_stream() builds: the calls of a small layer are bound by
+# the host (a route, plan and forward of 5 launches took 27 us to enqueue).
+_current_device = _raw_stream = None
 
 
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        global _current_device, _raw_stream
+        if _raw_stream is None:
+            import torch
+            _current_device = torch.cuda.current_device
+            _raw_stream = torch._C._cuda_getCurrentRawStream
+        return _raw_stream(_current_device())
     return stream if isinstance(stream, int) else stream.cuda_stream
 
 
@@ -198,7 +206,7 @@ def moe_workspace_region(shape: MoeShape, with_backward: bool, which: int):
 
 def moe_route(shape, X, W_r, bias, logits, topk_idx, topk_w, ws, ws_bytes=None, stream=None,
               raise_on_error=True):
-    nbytes = ws.numel() * ws.element_size() if ws_bytes is None else ws_bytes
+    nbytes = ws.nbytes if ws_bytes is None else ws_bytes
     st = lib().moe_route(ctypes.byref(shape), _p(X), _p(W_r), _p(bias), _p(logits), _p(topk_idx),
                          _p(topk_w), _p(ws), nbytes, _stream(stream))
     return _check("moe_route", st, raise_on_error)
@@ -220,7 +228,7 @@ def grads_struct(dW_gate, dW_up, dW_down, dW_r, dZ=None, dWg_s=None, dWu_s=None,
 
 def moe_plan(shape, topk_idx, plan: MoePlanBufs, ws, ws_bytes=None, stream=None,
              raise_on_error=True):
-    nbytes = ws.numel() * ws.element_size() if ws_bytes is None else ws_bytes
+    nbytes = ws.nbytes if ws_bytes is None else ws_bytes
     st = lib().moe_plan(ctypes.byref(shape), _p(topk_idx), ctypes.byref(plan), _p(ws), nbytes,
                         _stream(stream))
     return _check("moe_plan", st, raise_on_error)
@@ -239,7 +247,7 @@ def moe_schedule_workspace_bytes(R: int, NK: int, L: int) -> int:
 
 def moe_schedule(R, NK, L, c, A, M, S, phi, phi_rows, ws, ws_bytes=None, stream=None,
                  raise_on_error=True):
-    nbytes = ws.numel() * ws.element_size() if ws_bytes is None else ws_bytes
+    nbytes = ws.nbytes if ws_bytes is None else ws_bytes
     st = lib().moe_schedule(R, NK, L, c, _p(A), _p(M), _p(S), _p(phi), phi_rows, _p(ws), nbytes,
                             _stream(stream))
     return _check("moe_schedule", st, raise_on_error)
@@ -269,7 +277,7 @@ def moe_mx_quantize_weights_bwd(shape, weights: MoeWeights, mx: MoeMxBwdWeights,
 def moe_backward_mx(shape, dY, X, W_r, weights: MoeWeights, mx: MoeMxBwdWeights, topk_idx, topk_w,
                     plan: MoePlanBufs, dX, grads: MoeGrads, ws, ws_bytes=None, stream=None,
                     raise_on_error=True, wgrad_mxfp8=False):
-    nbytes = ws.numel() * ws.element_size() if ws_bytes is None else ws_bytes
+    nbytes = ws.nbytes if ws_bytes is None else ws_bytes
     st = lib().moe_backward_mx(ctypes.byref(shape), _p(dY), _p(X), _p(W_r), ctypes.byref(weights),
                                ctypes.byref(mx), _p(topk_idx), _p(topk_w), ctypes.byref(plan),
                                _p(dX), ctypes.byref(grads), int(wgrad_mxfp8), _p(ws), nbytes,
@@ -295,7 +303,7 @@ def moe_mx_quantize_weights(shape, weights: MoeWeights, mx: MoeMxWeights, stream
 def moe_forward_mx(shape, X, weights: MoeWeights, mx: MoeMxWeights, topk_idx, topk_w,
                    plan: MoePlanBufs, Y, ws, ws_bytes=None, stream=None, raise_on_error=True,
                    events: MoeStageEvents = None, save_for_backward=False):
-    nbytes = ws.numel() * ws.element_size() if ws_bytes is None else ws_bytes
+    nbytes = ws.nbytes if ws_bytes is None else ws_bytes
     st = lib().moe_forward_mx(ctypes.byref(shape), _p(X), ctypes.byref(weights), ctypes.byref(mx),
                               _p(topk_idx), _p(topk_w), ctypes.byref(plan), _p(Y),
                               int(bool(save_for_backward)), _p(ws), nbytes, _stream(stream),
@@ -312,7 +320,7 @@ def moe_dispatch(shape, X, plan: MoePlanBufs, Xperm, stream=None, raise_on_error
 def moe_forward(shape, X, weights: MoeWeights, topk_idx, topk_w, plan: MoePlanBufs, Y,
                 save_for_backward, ws, ws_bytes=None, stream=None, raise_on_error=True,
                 events: MoeStageEvents = None):
-    nbytes = ws.numel() * ws.element_size() if ws_bytes is None else ws_bytes
+    nbytes = ws.nbytes if ws_bytes is None else ws_bytes
     st = lib().moe_forward(ctypes.byref(shape), _p(X), ctypes.byref(weights), _p(topk_idx),
                            _p(topk_w), ctypes.byref(plan), _p(Y), int(bool(save_for_backward)),
                            _p(ws), nbytes, _stream(stream),
@@ -323,7 +331,7 @@ def moe_forward(shape, X, weights: MoeWeights, topk_idx, topk_w, plan: MoePlanBu
 def moe_backward(shape, dY, X, W_r, weights: MoeWeights, topk_idx, topk_w, plan: MoePlanBufs, dX,
                  grads: MoeGrads, ws, ws_bytes=None, stream=None, raise_on_error=True,
                  events: MoeStageEvents = None):
-    nbytes = ws.numel() * ws.element_size() if ws_bytes is None else ws_bytes
+    nbytes = ws.nbytes if ws_bytes is None else ws_bytes
     st = lib().moe_backward(ctypes.byref(shape), _p(dY), _p(X), _p(W_r), ctypes.byref(weights),
                             _p(topk_idx), _p(topk_w), ctypes.byref(plan), _p(dX),
                             ctypes.byref(grads), _p(ws), nbytes, _stream(stream),
@@ -339,7 +347,7 @@ def moe_ring_workspace_bytes(shape: MoeShape, ring_rows: int, with_backward: boo
 def moe_forward_ring(shape, X, weights: MoeWeights, topk_idx, topk_w, plan: MoePlanBufs, Y,
                      ring_rows, save_for_backward, ws, ws_bytes=None, stream=None,
                      raise_on_error=True):
-    nbytes = ws.numel() * ws.element_size() if ws_bytes is None else ws_bytes
+    nbytes = ws.nbytes if ws_bytes is None else ws_bytes
     st = lib().moe_forward_ring(ctypes.byref(shape), _p(X), ctypes.byref(weights), _p(topk_idx),
                                 _p(topk_w), ctypes.byref(plan), _p(Y), int(ring_rows),
                                 int(bool(save_for_backward)), _p(ws), nbytes, _stream(stream))
@@ -349,7 +357,7 @@ def moe_forward_ring(shape, X, weights: MoeWeights, topk_idx, topk_w, plan: MoeP
 def moe_backward_ring(shape, dY, X, W_r, weights: MoeWeights, topk_idx, topk_w,
                       plan: MoePlanBufs, dX, grads: MoeGrads, ring_rows, ws, ws_bytes=None,
                       stream=None, raise_on_error=True):
-    nbytes = ws.numel() * ws.element_size() if ws_bytes is None else ws_bytes
+    nbytes = ws.nbytes if ws_bytes is None else ws_bytes
     st = lib().moe_backward_ring(ctypes.byref(shape), _p(dY), _p(X), _p(W_r),
                                  ctypes.byref(weights), _p(topk_idx), _p(topk_w),
                                  ctypes.byref(plan), _p(dX), ctypes.byref(grads), int(ring_rows),
@@ -359,7 +367,7 @@ def moe_backward_ring(shape, dY, X, W_r, weights: MoeWeights, topk_idx, topk_w,
 
 def moe_forward_fused(shape, X, weights: MoeWeights, topk_idx, topk_w, plan: MoePlanBufs, Y,
                       save_for_backward, ws, ws_bytes=None, stream=None, raise_on_error=True):
-    nbytes = ws.numel() * ws.element_size() if ws_bytes is None else ws_bytes
+    nbytes = ws.nbytes if ws_bytes is None else ws_bytes
     st = lib().moe_forward_fused(ctypes.byref(shape), _p(X), ctypes.byref(weights), _p(topk_idx),
                                  _p(topk_w), ctypes.byref(plan), _p(Y),
                                  int(bool(save_for_backward)), _p(ws), nbytes, _stream(stream))
