@@ -14,6 +14,7 @@
 namespace {
 
 constexpr size_t ALIGN = 256;
+constexpr long DENSE_PARTS_MAX = 128;   // tiles of Y, half of the CUs
 
 size_t up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
@@ -25,7 +26,7 @@ struct Layout {
     size_t err, blockcounts, blockbase, blockflags, wrt, rpart, rowidx, wperm, zeros, fused;
     size_t prefix_total;
     size_t acc, coff;          // ring only: fp32 per-token accumulator, window regions
-    size_t A, B, H, Yexp, As, Bs, Hs, Ysh, part, part_s;
+    size_t A, B, H, Yexp, As, Bs, Hs, Ysh;
     size_t fwd_total;
     size_t dA, dB, Hw, dgpart, dg, dZ, dXperm, dAs, dBs, dXsh, dwr_part, dzs, wrs, xtt;
     size_t dytt;
@@ -46,6 +47,18 @@ struct Layout {
     long act_rows;             // rows of the per-route activation buffers
     int dg_parts;
 };
+
+// Dense routing on few token tiles: the folded down product has one workgroup
+// per 256 x 256 tile of Y and a K loop over every expert, so a short batch
+// leaves most CUs idle (200 tokens at d 7168: 28 workgroups of 288 K steps).
+// While it would fill at most half of them, the experts' products run as
+// tiles of their own into fp32 and a small kernel adds them in the same order
+// of experts.  Forward with 8 experts and a shared one (us), folded / in
+// parts: 200 tokens 706 / 387, 500 737 / 494, 1000 (112 workgroups) 913 / 846;
+// 1500 (168) 1185 / 1257, 2000 1386 / 1579: the fp32 traffic then costs more.
+bool dense_parts(const moe_shape &s) {
+    return s.k == s.E && s.T > 0 && (s.T + 255) / 256 * (s.d / 256) <= DENSE_PARTS_MAX;
+}
 
 // ring_rows < 0: per-route activations for all T*k routes; otherwise a ring
 // of ring_rows rows (bounded-memory execution).
@@ -77,19 +90,18 @@ Layout make_layout(const moe_shape &s, long ring_rows = -1) {
     L.A = take(Ra * f * 2);
     L.B = take(Ra * f * 2);
     L.H = take(Ra * f * 2);
-    L.Yexp = take(Ra * d * 2);
+    // Per-expert down products kept in fp32 (dense routing, small batches and
+    // short ones, see dense_parts) and the small batches' up/gate K slices lie
+    // over Yexp and Ysh; no two of these are live together.
+    const int tt = ring_rows < 0 ? skinny_tiles((long)T, (long)R, (int)E) : 0;
+    const bool part = ring_rows < 0 && s.k == s.E && (tt > 0 || dense_parts(s));
+    L.kslices = tt > 0 ? skinny_kslices((long)T, (long)R, (int)E, (int)d, (int)f, (int)fs, tt) : 1;
+    const size_t upw = L.kslices > 1 ? 2 * (size_t)L.kslices : 0;
+    L.Yexp = take(std::max(Ra * d * (part ? 4 : 2), upw * R * f * 4));
     L.As = take(T * fs * 2);
     L.Bs = take(T * fs * 2);
     L.Hs = take(T * fs * 2);
-    L.Ysh = take(T * d * 2);
-    // small batches with dense routing: the down products before their sum, fp32
-    // and the up/gate products' K slices (the two are never live together)
-    const int tt = ring_rows < 0 ? skinny_tiles((long)T, (long)R, (int)E) : 0;
-    const bool part = tt > 0 && s.k == s.E;
-    L.kslices = tt > 0 ? skinny_kslices((long)T, (long)R, (int)E, (int)d, (int)f, (int)fs, tt) : 1;
-    const size_t upw = L.kslices > 1 ? 2 * (size_t)L.kslices : 0;
-    L.part = take(std::max(part ? R * d * 4 : 0, upw * R * f * 4));
-    L.part_s = take(std::max(part && fs > 0 ? T * d * 4 : 0, upw * T * fs * 4));
+    L.Ysh = take(std::max(T * d * (part ? 4 : 2), upw * T * fs * 4));
     L.fwd_total = o;
     L.dg_parts = (int)(f / 128);   // BF16 dgrad: one per 128 columns (MXFP8: per 256)
     L.dA = take(Ra * f * 2);
@@ -374,7 +386,7 @@ hipError_t small_forward(const moe_shape &sh, const Layout &L, void *ws, const m
     u.C = at<uint16_t>(ws, L.H); u.ldc = f;
     u.row_w = dense ? topk_w : nullptr;
     u.kslices = L.kslices;
-    u.Cf = at<float>(ws, L.part); u.Cfs = at<float>(ws, L.part_s);
+    u.Cf = at<float>(ws, L.Yexp); u.Cfs = at<float>(ws, L.Ysh);
     if (fs > 0) {
         u.As = X; u.lda_s = d; u.Ks = d; u.Ns = fs;
         u.Bs = w->Wg_s; u.Bs2 = w->Wu_s; u.ldb_s = fs;
@@ -387,12 +399,12 @@ hipError_t small_forward(const moe_shape &sh, const Layout &L, void *ws, const m
     n.A = at<uint16_t>(ws, L.H); n.lda = f; n.a_nrows = R; n.K = f; n.N = d;
     n.B = w->W_down; n.ldb = d; n.b_estride = (long)f * d;
     n.ldc = d;
-    if (dense) n.Cf = at<float>(ws, L.part);
+    if (dense) n.Cf = at<float>(ws, L.Yexp);
     else n.C = at<uint16_t>(ws, L.Yexp);
     if (fs > 0) {
         n.As = at<uint16_t>(ws, L.Hs); n.lda_s = fs; n.Ks = fs; n.Ns = d;
         n.Bs = w->Wd_s; n.ldb_s = d; n.ldc_s = d;
-        if (dense) n.Cfs = at<float>(ws, L.part_s);
+        if (dense) n.Cfs = at<float>(ws, L.Ysh);
         else n.Cs = at<uint16_t>(ws, L.Ysh);
     }
     if ((e = launch_skinny_down(n, tt, s)) != hipSuccess) return e;
@@ -678,6 +690,40 @@ GemmArgs dx_cmb_args(const moe_shape &sh, const Layout &L, void *ws, const moe_w
     return g;
 }
 
+// The forward with dense routing, after the prologue: H keeps w h, and the
+// down product adds every expert and the shared expert into Y (stages 4 and 5
+// are empty), or each expert's product goes to fp32 first (dense_parts).
+hipError_t dense_forward(const moe_shape &sh, const Layout &L, void *ws, const moe_bf16 *X,
+                         const moe_weights *w, const moe_plan_bufs *plan, moe_bf16 *Y, bool save,
+                         const StageMarks &mk, hipStream_t s) {
+    const int T = (int)sh.T, E = (int)sh.E, d = (int)sh.d;
+    const Window all{plan->offsets, 0, (int)(sh.T * sh.k)};
+    GemmArgs gu = up_args(sh, L, ws, X, w, all, true, save);
+    gu.rowscale = at<float>(ws, L.wperm);
+    hipError_t e;
+    if ((e = launch_gemm_fwd_up(gu, all.count(), E, s)) != hipSuccess) return e;
+    if ((e = mk.mark(2)) != hipSuccess) return e;
+    if (sh.f_shared > 0 && (e = shared_up(sh, L, ws, X, w, save, s)) != hipSuccess) return e;
+    if ((e = mk.mark(3)) != hipSuccess) return e;
+    if (dense_parts(sh)) {
+        GemmArgs g = down_args(sh, L, ws, w, all);
+        g.Cf = at<float>(ws, L.Yexp);
+        if ((e = launch_gemm_fwd_down(g, all.count(), E, s)) != hipSuccess) return e;
+        const bool shared = sh.f_shared > 0;
+        if (shared) {
+            GemmArgs gs = shared_down_args(sh, L, ws, w);
+            gs.Cf = at<float>(ws, L.Ysh);
+            if ((e = launch_gemm_fwd_down(gs, T, 1, s)) != hipSuccess) return e;
+        }
+        e = launch_dense_sum(g.Cf, shared ? at<float>(ws, L.Ysh) : nullptr, plan->offsets, E, T,
+                             T * (int)sh.k, d, Y, s);
+    } else {
+        e = launch_gemm_fwd_down_cmb(down_cmb_args(sh, L, ws, w, plan->offsets, Y), s);
+    }
+    for (int i = 4; e == hipSuccess && i <= 6; ++i) e = mk.mark(i);
+    return e;
+}
+
 moe_status check_backward_args(const moe_shape *shape, const moe_bf16 *dY, const moe_bf16 *X,
                                const moe_bf16 *W_r, const moe_weights *weights,
                                const int32_t *topk_idx, const float *topk_w,
@@ -901,18 +947,7 @@ moe_status moe_forward(const moe_shape *shape, const moe_bf16 *X, const moe_weig
                         at<float>(ws, L.wperm), at<uint16_t>(ws, L.zeros), s));
     MOE_TRY(mk.mark(1));
     if (dense_routing(*shape)) {
-        // H keeps w h; the down product adds every expert and the shared
-        // expert into Y (stages 4 and 5 are empty)
-        GemmArgs gu = up_args(*shape, L, ws, X, weights, all, true, save_for_backward != 0);
-        gu.rowscale = at<float>(ws, L.wperm);
-        MOE_TRY(launch_gemm_fwd_up(gu, all.count(), E, s));
-        MOE_TRY(mk.mark(2));
-        if (fs > 0) MOE_TRY(shared_up(*shape, L, ws, X, weights, save_for_backward != 0, s));
-        MOE_TRY(mk.mark(3));
-        MOE_TRY(launch_gemm_fwd_down_cmb(down_cmb_args(*shape, L, ws, weights, plan->offsets, Y), s));
-        MOE_TRY(mk.mark(4));
-        MOE_TRY(mk.mark(5));
-        MOE_TRY(mk.mark(6));
+        MOE_TRY(dense_forward(*shape, L, ws, X, weights, plan, Y, save_for_backward != 0, mk, s));
         return MOE_OK;
     }
     MOE_TRY(routed_up(*shape, L, ws, X, weights, all, true, save_for_backward != 0, s));
@@ -956,6 +991,10 @@ moe_status moe_forward_fused(const moe_shape *shape, const moe_bf16 *X, const mo
                         at<float>(ws, L.wperm), at<uint16_t>(ws, L.zeros), s));
     const GemmArgs none;
     const bool dense = dense_routing(*shape);
+    if (dense && dense_parts(*shape)) {   // few tiles: moe_forward's launches
+        MOE_TRY(dense_forward(*shape, L, ws, X, weights, plan, Y, save, StageMarks{nullptr, s}, s));
+        return MOE_OK;
+    }
     GemmArgs gu = up_args(*shape, L, ws, X, weights, all, true, save);
     if (dense) gu.rowscale = at<float>(ws, L.wperm);
     MOE_TRY(launch_fused_forward(shared ? shared_up_args(*shape, L, ws, X, weights, save) : none, gu,

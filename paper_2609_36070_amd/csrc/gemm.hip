@@ -863,6 +863,10 @@ DEV void gemm_tile(const GemmArgs &g, const int *__restrict__ a_rows, const int 
                 f32x8 v = read8(row, c);
                 if (p >= row_end) continue;
                 const long o = (long)p * g.ldc + n0 + wn * WN + c;
+                if (MODE == FWD_DOWN && g.Cf) {   // fp32 products of dense routing, summed later
+                    st_f32x8(g.Cf + o, v);
+                    continue;
+                }
                 if (Tr::CMB && g.Cf) {
                     if (g.accumulate) {
                         const f32x8 prev = ld_f32x8(g.Cf + o);

@@ -37,6 +37,19 @@ def test_small_batch_parity(w):
 
 
 @pytest.mark.parametrize("w", [
+    # dense routing past the small batches: 121 tiles of Y (the experts' products
+    # summed from fp32), 132 (the folded product); both keep their activations
+    # for the backward's sake in the second pair
+    Workload("parts", T=2800, d=2816, E=2, k=2, f=256, f_s=512),
+    Workload("folded", T=2900, d=2816, E=2, k=2, f=256, f_s=512),
+    Workload("parts_train", T=130, d=512, E=9, k=9, f=256, backward=True),
+    Workload("folded_train", T=16700, d=512, E=2, k=2, f=256, f_s=256, backward=True),
+], ids=lambda w: w.name)
+def test_dense_down_products(w):
+    forward_parity(w, seed=32)
+
+
+@pytest.mark.parametrize("w", [
     Workload("sparse", T=48, d=512, E=16, k=4, f=256, f_s=256, bias_std=1.0),
     Workload("dense", T=48, d=512, E=4, k=4, f=256, f_s=256),
 ], ids=lambda w: w.name)
