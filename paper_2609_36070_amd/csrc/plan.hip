@@ -252,6 +252,7 @@ __global__ __launch_bounds__(1024) void plan_place_kernel(const int *__restrict_
         const int j = j0 + l + 64 * q;
         ev[q] = (q < per && j < j1) ? idx[j] : 0;
     }
+    int flag = 0;
     if constexpr (MULTI) {
         // a quarter of the blocks' histograms per 256 threads
         const int nb = gridDim.x, e = threadIdx.x & 255, h = threadIdx.x >> 8;
@@ -270,10 +271,10 @@ __global__ __launch_bounds__(1024) void plan_place_kernel(const int *__restrict_
         }
         before[h][e] = pre;
         all[h][e] = sum;
-        if (b == 0 && threadIdx.x < nb && blockflags[threadIdx.x]) anybad = 1;
+        if (b == 0 && threadIdx.x < nb) flag = blockflags[threadIdx.x];
     }
     __syncthreads();
-    int bad = 0;
+    int bad = flag;
 #pragma unroll
     for (int q = 0; q < NG; ++q) {
         if (q >= per || j0 + l + 64 * q >= j1) break;
