@@ -93,7 +93,8 @@ Layout make_layout(const moe_shape &s, long ring_rows = -1) {
     // Per-expert down products kept in fp32 (dense routing, small batches and
     // short ones, see dense_parts) and the small batches' up/gate K slices lie
     // over Yexp and Ysh; no two of these are live together.
-    const int tt = ring_rows < 0 ? skinny_tiles((long)T, (long)R, (int)E) : 0;
+    // (A ring of all the rows runs a small batch as moe_forward does.)
+    const int tt = ring_rows < 0 || Ra == R ? skinny_tiles((long)T, (long)R, (int)E) : 0;
     const bool part = ring_rows < 0 && s.k == s.E && (tt > 0 || dense_parts(s));
     L.kslices = tt > 0 ? skinny_kslices((long)T, (long)R, (int)E, (int)d, (int)f, (int)fs, tt) : 1;
     const size_t upw = L.kslices > 1 ? 2 * (size_t)L.kslices : 0;

@@ -38,8 +38,8 @@ def test_small_batch_parity(w):
 
 @pytest.mark.parametrize("w", [
     # dense routing past the small batches: 121 tiles of Y (the experts' products
-    # summed from fp32), 132 (the folded product); both keep their activations
-    # for the backward's sake in the second pair
+    # summed from fp32) and 132 (the folded product), then the same with the
+    # activations kept
     Workload("parts", T=2800, d=2816, E=2, k=2, f=256, f_s=512),
     Workload("folded", T=2900, d=2816, E=2, k=2, f=256, f_s=512),
     Workload("parts_train", T=130, d=512, E=9, k=9, f=256, backward=True),
@@ -71,3 +71,15 @@ def test_small_batch_against_tile_gemms(w):
         L.step()
         torch.cuda.synchronize()
         assert torch.equal(L.Y, y)
+
+
+@pytest.mark.parametrize("d", [512, 2304])
+def test_small_batch_in_one_window_ring(d):
+    """A ring holding every route runs a small batch as the one-pass forward
+    does, K slices included: the same bits."""
+    w = Workload("ring", T=30, d=d, E=8, k=2, f=256, f_s=256, bias_std=0.5)
+    inp = make_inputs(w, 34)
+    full, ring = DeviceLayer(w, inp), DeviceLayer(w, inp, ring_rows=w.T * w.k)
+    full.step(), ring.step()
+    torch.cuda.synchronize()
+    assert torch.equal(full.Y, ring.Y)
