@@ -1061,8 +1061,6 @@ hipError_t launch_mode(GemmArgs g, int tiles_m, int ntn, hipStream_t st, long gr
 
 }  // namespace
 
-int gemm_tile_m() { return BM; }
-
 // m-tile slots of a row problem.  Grouped: an upper bound on
 // sum_e ceil(M_e / BM), which is at most rows / BM + groups; slots past the
 // actual tiles return at once.

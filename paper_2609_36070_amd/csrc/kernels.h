@@ -82,7 +82,6 @@ struct GemmArgs {
     const int *tok_offsets = nullptr;
 };
 
-int gemm_tile_m();
 hipError_t launch_gemm_fwd_up(const GemmArgs &g, long rows, int groups, hipStream_t st);
 hipError_t launch_gemm_fwd_down(const GemmArgs &g, long rows, int groups, hipStream_t st);
 hipError_t launch_gemm_bwd_dgrad(const GemmArgs &g, long rows, int groups, hipStream_t st);

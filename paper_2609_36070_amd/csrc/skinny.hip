@@ -318,8 +318,10 @@ hipError_t launch_mode(SkinnyArgs g, int tt, hipStream_t st) {
 // 64-row tiles from 17 tokens up: more rows per pass over the weights beat
 // the smaller tiles' higher occupancy at every mean row count (128 experts, us
 // with 16 / 32 / 64 rows: 256 tokens 306 / 284 / 280, 512: 393 / 338 / 315);
-// up to 16 tokens no expert has more than 16 rows.  Past 64 rows per expert
-// on average the tile GEMMs catch up (32 experts, 250 tokens: 392 against 395).
+// up to 16 tokens no expert has more than 16 rows.  About 64 rows per expert
+// on average the tile GEMMs catch up, as more experts take a second tile (us
+// here / there: 32 experts, 150 tokens 285 / 361, 200: 309 / 359, 250: 373 /
+// 358; 128 experts, 512 tokens 297 / 354, 1000: 361 / 386).
 int skinny_tiles(long T, long R, int E) {
     if (T <= 0) return 0;
     if (T <= 16) return 1;
