@@ -503,19 +503,23 @@ __global__ __launch_bounds__(NTHREADS, 1) void gemm_mx_kernel(MxGemmArgs g, cons
         }
     } else if constexpr (MODE == MX_WGRAD) {
         // fp32 rows of dW[e]; M and N are multiples of the tile, so every
-        // staged row is a real one
-        constexpr int LPR = WN / 8, RPP = 64 / LPR;
+        // staged row is a real one.  With some 1500 rows per expert a third of
+        // a tile's time is its 256 KB of output, so the lanes of a store write
+        // one contiguous run (with 8 columns per lane each store leaves every
+        // other 16 bytes) and past L2, which holds the operand panels: 4096 x
+        // 1536, 32 experts, 48000 rows, the three products 1774 -> 1597 us
+        // (contiguous but cached: 1711).
+        constexpr int LPR = WN / 4, RPP = 64 / LPR;
         float *out = g.Cf + (long)e * g.M * g.N;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             stage(i);
 #pragma unroll
             for (int t = 0; t < 32 / RPP; ++t) {
-                const int row = lane / LPR + RPP * t, c = 8 * (lane % LPR);
-                const f32x8 v = read8(row, c);
+                const int row = lane / LPR + RPP * t, c = 4 * (lane % LPR);
+                const f32x4_t v = *reinterpret_cast<const f32x4_t *>(scr + row * SP + c);
                 float *o = out + (long)(row0 + wm * WM + 32 * i + row) * g.N + n0 + wn * WN + c;
-                *reinterpret_cast<f32x4_t *>(o) = f32x4_t{v[0], v[1], v[2], v[3]};
-                *reinterpret_cast<f32x4_t *>(o + 4) = f32x4_t{v[4], v[5], v[6], v[7]};
+                __builtin_nontemporal_store(v, reinterpret_cast<f32x4_t *>(o));
             }
         }
     } else {   // MX_DOWN, MX_DX: bf16 rows
