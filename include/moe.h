@@ -61,7 +61,7 @@ typedef enum {
     MOE_OK = 0,
     MOE_EINVAL = 1,        /* null/misaligned pointer, bad dimension, k > E */
     MOE_EUNSUPPORTED = 2,  /* valid but outside the limits above */
-    MOE_ENOSPACE = 3,      /* workspace smaller than moe_workspace_bytes() */
+    MOE_ENOSPACE = 3,      /* workspace too small (moe_workspace_bytes() is enough) */
     MOE_EHIP = 4           /* a HIP launch was rejected */
 } moe_status;
 
@@ -190,9 +190,14 @@ typedef struct {
     void *ev[MOE_MAX_STAGE_EVENTS];
 } moe_stage_events;
 
-/* Workspace bytes needed by moe_route/moe_plan/moe_forward (with_backward=0)
- * or additionally moe_backward (with_backward=1).  Pure host function;
- * returns 0 for an invalid or unsupported shape. */
+/* Workspace bytes of moe_route/moe_plan/moe_forward (with_backward=0) or
+ * additionally moe_backward (with_backward=1): the regions below, and room for
+ * the fp32 partial results that short batches use (past the forward's regions,
+ * over those of the backward).  It never falls as T grows, so a workspace made
+ * for the largest batch serves every smaller one.  A workspace that holds the
+ * regions alone is accepted too; a short batch then runs without the partial
+ * results, slower and summed in another order.  Pure host function; returns 0
+ * for an invalid or unsupported shape. */
 size_t moe_workspace_bytes(const moe_shape *shape, int with_backward);
 
 /* Byte offset and size of a named workspace region (host only). */

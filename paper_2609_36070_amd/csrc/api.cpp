@@ -43,7 +43,6 @@ struct Layout {
     size_t da32, db32, hw32;   // their fp32 sources dA, dB, w h (plan order)
     size_t mxw_total;
     long tpad;                 // their row pitch: the padded token positions' bound
-    int kslices;               // small batches: workgroups sharing an up/gate tile's K
     long act_rows;             // rows of the per-route activation buffers
     int dg_parts;
 };
@@ -90,19 +89,11 @@ Layout make_layout(const moe_shape &s, long ring_rows = -1) {
     L.A = take(Ra * f * 2);
     L.B = take(Ra * f * 2);
     L.H = take(Ra * f * 2);
-    // Per-expert down products kept in fp32 (dense routing, small batches and
-    // short ones, see dense_parts) and the small batches' up/gate K slices lie
-    // over Yexp and Ysh; no two of these are live together.
-    // (A ring of all the rows runs a small batch as moe_forward does.)
-    const int tt = ring_rows < 0 || Ra == R ? skinny_tiles((long)T, (long)R, (int)E) : 0;
-    const bool part = ring_rows < 0 && s.k == s.E && (tt > 0 || dense_parts(s));
-    L.kslices = tt > 0 ? skinny_kslices((long)T, (long)R, (int)E, (int)d, (int)f, (int)fs, tt) : 1;
-    const size_t upw = L.kslices > 1 ? 2 * (size_t)L.kslices : 0;
-    L.Yexp = take(std::max(Ra * d * (part ? 4 : 2), upw * R * f * 4));
+    L.Yexp = take(Ra * d * 2);
     L.As = take(T * fs * 2);
     L.Bs = take(T * fs * 2);
     L.Hs = take(T * fs * 2);
-    L.Ysh = take(std::max(T * d * (part ? 4 : 2), upw * T * fs * 4));
+    L.Ysh = take(T * d * 2);
     L.fwd_total = o;
     L.dg_parts = (int)(f / 128);   // BF16 dgrad: one per 128 columns (MXFP8: per 256)
     L.dA = take(Ra * f * 2);
@@ -370,11 +361,72 @@ int small_tiles(const moe_shape &sh, int save) {
     return skinny_tiles((long)sh.T, (long)R, (int)sh.E);
 }
 
+// Rows of a ring's per-route activations.
+long ring_act_rows(const moe_shape &sh, int64_t ring_rows) {
+    const long R = (long)sh.T * sh.k;
+    return ring_rows < R ? (long)ring_rows : R;
+}
+
+// How a one-pass forward runs.  Its fp32 partial results (the K slices of a
+// small batch's up/gate product, then the experts' down products of dense
+// routing; the former are consumed before the latter are written) lie past the
+// forward's layout, over regions that only a backward uses.
+struct FwdPath {
+    int tt = 0;                       // small batch: 16-row tiles per workgroup (0: the tile GEMMs)
+    int kslices = 1;                  // small batch: workgroups sharing an up/gate tile's K
+    bool parts = false;               // dense routing: down products in fp32, then added
+    size_t at_s = 0, bytes = 0;       // scratch: start of the shared expert's, size
+};
+
+// `room`: bytes of workspace past the forward's layout.  moe_workspace_bytes
+// has room for every shape's scratch; a workspace that holds the layout alone
+// is still enough, for the paths that need none.
+FwdPath forward_path(const moe_shape &sh, int save, size_t room) {
+    const size_t T = sh.T, R = T * (size_t)sh.k, d = sh.d, f = sh.f, fs = sh.f_shared;
+    const bool dense = dense_routing(sh);
+    FwdPath p;
+    p.tt = small_tiles(sh, save);
+    if (p.tt) p.kslices = skinny_kslices((long)T, (long)R, (int)sh.E, (int)d, (int)f, (int)fs, p.tt);
+    p.parts = dense && (p.tt || dense_parts(sh));
+    const size_t slices = p.kslices > 1 ? 8 * (size_t)p.kslices : 0, part = p.parts ? 4 : 0;
+    p.at_s = up(std::max(slices * R * f, part * R * d));
+    p.bytes = p.at_s + up(fs ? std::max(slices * T * fs, part * T * d) : 0);
+    if (p.bytes <= room) return p;
+    FwdPath q;
+    q.tt = dense ? 0 : p.tt;
+    return q;
+}
+
+// Workspace of a one-pass forward (ring_rows < 0) or a ring of ring_rows rows:
+// the layout, and room for the scratch.  The scratch exists for few tokens
+// only, so its largest need over all smaller batches counts: a workspace
+// sized for T tokens serves fewer on the same path.  Each bound below grows
+// with its number of tokens, and a ring uses scratch while it is one window.
+size_t forward_bytes(const moe_shape &sh, int64_t ring_rows = -1) {
+    auto layout = [&](int64_t t) {
+        moe_shape q = sh;
+        q.T = t;
+        return make_layout(q, ring_rows < 0 ? -1 : ring_act_rows(q, ring_rows)).fwd_total;
+    };
+    size_t need = layout(sh.T);
+    const int64_t tmax = ring_rows < 0 ? sh.T : std::min(sh.T, ring_rows / sh.k);
+    auto with = [&](int64_t t, size_t scratch) { need = std::max(need, layout(t) + scratch + 2 * ALIGN); };
+    const int64_t ts = std::min(tmax, (int64_t)skinny_max_tokens((int)sh.E, (int)sh.k));
+    if (ts > 0 && skinny_max_slices((int)sh.d) > 1)
+        with(ts, std::min(SK_SLICE_BYTES,
+                          8 * (size_t)skinny_max_slices((int)sh.d) * (size_t)ts * (sh.k * sh.f + sh.f_shared)));
+    const int64_t td = std::min(tmax, std::max(int64_t(64), DENSE_PARTS_MAX / (sh.d / 256) * 256));
+    if (dense_routing(sh) && td > 0) with(td, 4 * (size_t)td * (size_t)(sh.k + (sh.f_shared > 0)) * sh.d);
+    return need;
+}
+
 // The forward of a small batch: up/gate and down of every routed expert and
 // the shared one in a launch each, then the sum over each token's experts.
 hipError_t small_forward(const moe_shape &sh, const Layout &L, void *ws, const moe_bf16 *X,
                          const moe_weights *w, const float *topk_w, const moe_plan_bufs *plan,
-                         moe_bf16 *Y, int tt, const StageMarks &mk, hipStream_t s) {
+                         moe_bf16 *Y, const FwdPath &path, const StageMarks &mk, hipStream_t s) {
+    const int tt = path.tt;
+    float *part = at<float>(ws, L.fwd_total), *part_s = at<float>(ws, L.fwd_total + path.at_s);
     const int T = (int)sh.T, d = (int)sh.d, E = (int)sh.E, k = (int)sh.k, f = (int)sh.f;
     const int fs = (int)sh.f_shared, R = T * k;
     const bool dense = dense_routing(sh);
@@ -386,8 +438,8 @@ hipError_t small_forward(const moe_shape &sh, const Layout &L, void *ws, const m
     u.B = w->W_gate; u.B2 = w->W_up; u.ldb = f; u.b_estride = (long)d * f;
     u.C = at<uint16_t>(ws, L.H); u.ldc = f;
     u.row_w = dense ? topk_w : nullptr;
-    u.kslices = L.kslices;
-    u.Cf = at<float>(ws, L.Yexp); u.Cfs = at<float>(ws, L.Ysh);
+    u.kslices = path.kslices;
+    u.Cf = part; u.Cfs = part_s;
     if (fs > 0) {
         u.As = X; u.lda_s = d; u.Ks = d; u.Ns = fs;
         u.Bs = w->Wg_s; u.Bs2 = w->Wu_s; u.ldb_s = fs;
@@ -400,12 +452,12 @@ hipError_t small_forward(const moe_shape &sh, const Layout &L, void *ws, const m
     n.A = at<uint16_t>(ws, L.H); n.lda = f; n.a_nrows = R; n.K = f; n.N = d;
     n.B = w->W_down; n.ldb = d; n.b_estride = (long)f * d;
     n.ldc = d;
-    if (dense) n.Cf = at<float>(ws, L.Yexp);
+    if (dense) n.Cf = part;
     else n.C = at<uint16_t>(ws, L.Yexp);
     if (fs > 0) {
         n.As = at<uint16_t>(ws, L.Hs); n.lda_s = fs; n.Ks = fs; n.Ns = d;
         n.Bs = w->Wd_s; n.ldb_s = d; n.ldc_s = d;
-        if (dense) n.Cfs = at<float>(ws, L.Ysh);
+        if (dense) n.Cfs = part_s;
         else n.Cs = at<uint16_t>(ws, L.Ysh);
     }
     if ((e = launch_skinny_down(n, tt, s)) != hipSuccess) return e;
@@ -693,10 +745,10 @@ GemmArgs dx_cmb_args(const moe_shape &sh, const Layout &L, void *ws, const moe_w
 
 // The forward with dense routing, after the prologue: H keeps w h, and the
 // down product adds every expert and the shared expert into Y (stages 4 and 5
-// are empty), or each expert's product goes to fp32 first (dense_parts).
+// are empty), or each expert's product goes to fp32 first (path.parts).
 hipError_t dense_forward(const moe_shape &sh, const Layout &L, void *ws, const moe_bf16 *X,
                          const moe_weights *w, const moe_plan_bufs *plan, moe_bf16 *Y, bool save,
-                         const StageMarks &mk, hipStream_t s) {
+                         const FwdPath &path, const StageMarks &mk, hipStream_t s) {
     const int T = (int)sh.T, E = (int)sh.E, d = (int)sh.d;
     const Window all{plan->offsets, 0, (int)(sh.T * sh.k)};
     GemmArgs gu = up_args(sh, L, ws, X, w, all, true, save);
@@ -706,18 +758,18 @@ hipError_t dense_forward(const moe_shape &sh, const Layout &L, void *ws, const m
     if ((e = mk.mark(2)) != hipSuccess) return e;
     if (sh.f_shared > 0 && (e = shared_up(sh, L, ws, X, w, save, s)) != hipSuccess) return e;
     if ((e = mk.mark(3)) != hipSuccess) return e;
-    if (dense_parts(sh)) {
+    if (path.parts) {
         GemmArgs g = down_args(sh, L, ws, w, all);
-        g.Cf = at<float>(ws, L.Yexp);
+        g.Cf = at<float>(ws, L.fwd_total);
         if ((e = launch_gemm_fwd_down(g, all.count(), E, s)) != hipSuccess) return e;
         const bool shared = sh.f_shared > 0;
         if (shared) {
             GemmArgs gs = shared_down_args(sh, L, ws, w);
-            gs.Cf = at<float>(ws, L.Ysh);
+            gs.Cf = at<float>(ws, L.fwd_total + path.at_s);
             if ((e = launch_gemm_fwd_down(gs, T, 1, s)) != hipSuccess) return e;
         }
-        e = launch_dense_sum(g.Cf, shared ? at<float>(ws, L.Ysh) : nullptr, plan->offsets, E, T,
-                             T * (int)sh.k, d, Y, s);
+        e = launch_dense_sum(g.Cf, shared ? at<float>(ws, L.fwd_total + path.at_s) : nullptr, plan->offsets,
+                             E, T, T * (int)sh.k, d, Y, s);
     } else {
         e = launch_gemm_fwd_down_cmb(down_cmb_args(sh, L, ws, w, plan->offsets, Y), s);
     }
@@ -753,11 +805,6 @@ moe_status check_ring(int64_t ring_rows) {
     if (ring_rows < 1) return MOE_EINVAL;
     if (ring_rows >= (int64_t(1) << 31)) return MOE_EUNSUPPORTED;
     return MOE_OK;
-}
-
-long ring_act_rows(const moe_shape &sh, int64_t ring_rows) {
-    const long R = (long)sh.T * sh.k;
-    return ring_rows < R ? (long)ring_rows : R;
 }
 
 int ring_windows(const moe_shape &sh, int64_t ring_rows) {
@@ -803,8 +850,8 @@ extern "C" {
 
 size_t moe_workspace_bytes(const moe_shape *shape, int with_backward) {
     if (check_shape(shape) != MOE_OK) return 0;
-    const Layout L = make_layout(*shape);
-    return with_backward ? L.bwd_total : L.fwd_total;
+    const size_t fwd = forward_bytes(*shape);
+    return with_backward ? std::max(make_layout(*shape).bwd_total, fwd) : fwd;
 }
 
 moe_status moe_workspace_region(const moe_shape *shape, int with_backward, moe_ws_tensor which,
@@ -939,16 +986,17 @@ moe_status moe_forward(const moe_shape *shape, const moe_bf16 *X, const moe_weig
     const StageMarks mk{events, s};
 
     MOE_TRY(mk.mark(0));
-    if (const int tt = small_tiles(*shape, save_for_backward)) {
+    const FwdPath path = forward_path(*shape, save_for_backward, ws_bytes - L.fwd_total);
+    if (path.tt) {
         MOE_TRY(mk.mark(1));
-        MOE_TRY(small_forward(*shape, L, ws, X, weights, topk_w, plan, Y, tt, mk, s));
+        MOE_TRY(small_forward(*shape, L, ws, X, weights, topk_w, plan, Y, path, mk, s));
         return MOE_OK;
     }
     MOE_TRY(launch_prep(plan->perm, plan->offsets, E, topk_w, k, T, at<int>(ws, L.rowidx),
                         at<float>(ws, L.wperm), at<uint16_t>(ws, L.zeros), s));
     MOE_TRY(mk.mark(1));
     if (dense_routing(*shape)) {
-        MOE_TRY(dense_forward(*shape, L, ws, X, weights, plan, Y, save_for_backward != 0, mk, s));
+        MOE_TRY(dense_forward(*shape, L, ws, X, weights, plan, Y, save_for_backward != 0, path, mk, s));
         return MOE_OK;
     }
     MOE_TRY(routed_up(*shape, L, ws, X, weights, all, true, save_for_backward != 0, s));
@@ -983,8 +1031,9 @@ moe_status moe_forward_fused(const moe_shape *shape, const moe_bf16 *X, const mo
     const Window all{plan->offsets, 0, (int)R};
     const bool save = save_for_backward != 0;
     // a small batch has nothing to overlap: moe_forward's launches
-    if (const int tt = small_tiles(*shape, save_for_backward)) {
-        MOE_TRY(small_forward(*shape, L, ws, X, weights, topk_w, plan, Y, tt, StageMarks{nullptr, s}, s));
+    const FwdPath path = forward_path(*shape, save_for_backward, ws_bytes - L.fwd_total);
+    if (path.tt) {
+        MOE_TRY(small_forward(*shape, L, ws, X, weights, topk_w, plan, Y, path, StageMarks{nullptr, s}, s));
         return MOE_OK;
     }
 
@@ -992,8 +1041,8 @@ moe_status moe_forward_fused(const moe_shape *shape, const moe_bf16 *X, const mo
                         at<float>(ws, L.wperm), at<uint16_t>(ws, L.zeros), s));
     const GemmArgs none;
     const bool dense = dense_routing(*shape);
-    if (dense && dense_parts(*shape)) {   // few tiles: moe_forward's launches
-        MOE_TRY(dense_forward(*shape, L, ws, X, weights, plan, Y, save, StageMarks{nullptr, s}, s));
+    if (path.parts) {   // few tiles: moe_forward's launches
+        MOE_TRY(dense_forward(*shape, L, ws, X, weights, plan, Y, save, path, StageMarks{nullptr, s}, s));
         return MOE_OK;
     }
     GemmArgs gu = up_args(*shape, L, ws, X, weights, all, true, save);
@@ -1083,8 +1132,9 @@ moe_status moe_backward(const moe_shape *shape, const moe_bf16 *dY, const moe_bf
 
 size_t moe_ring_workspace_bytes(const moe_shape *shape, int64_t ring_rows, int with_backward) {
     if (check_shape(shape) != MOE_OK || check_ring(ring_rows) != MOE_OK) return 0;
+    const size_t fwd = forward_bytes(*shape, ring_rows);
     const Layout L = make_layout(*shape, ring_act_rows(*shape, ring_rows));
-    return with_backward ? L.bwd_total : L.fwd_total;
+    return with_backward ? std::max(L.bwd_total, fwd) : fwd;
 }
 
 moe_status moe_forward_ring(const moe_shape *shape, const moe_bf16 *X, const moe_weights *weights,
@@ -1107,9 +1157,11 @@ moe_status moe_forward_ring(const moe_shape *shape, const moe_bf16 *X, const moe
     const int nwin = ring_windows(*shape, ring_rows);
     int *coff = at<int>(ws, L.coff);
 
-    const int tt = nwin == 1 && !dense_routing(*shape) ? small_tiles(*shape, save_for_backward) : 0;
-    if (tt) {   // one window holds every route: the one-pass forward
-        MOE_TRY(small_forward(*shape, L, ws, X, weights, topk_w, plan, Y, tt, StageMarks{nullptr, s}, s));
+    FwdPath path;
+    if (nwin == 1 && !dense_routing(*shape))
+        path = forward_path(*shape, save_for_backward, ws_bytes - L.fwd_total);
+    if (path.tt) {   // one window holds every route: the one-pass forward
+        MOE_TRY(small_forward(*shape, L, ws, X, weights, topk_w, plan, Y, path, StageMarks{nullptr, s}, s));
         return MOE_OK;
     }
     MOE_TRY(launch_prep(plan->perm, plan->offsets, E, topk_w, k, T, at<int>(ws, L.rowidx),

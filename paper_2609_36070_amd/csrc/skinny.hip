@@ -334,15 +334,26 @@ int skinny_tiles(long T, long R, int E) {
 // workgroups (2.5 per CU) K is split over two or four, if each keeps 1024
 // rows, and the SwiGLU moves to a small launch: 137 + 8 us.  Whole forward at
 // 1 / 2 / 4 slices (us): 61 tokens 267 / 241 / 232, 1 token 212 / 195 / 182;
-// 32 experts, d 4096, 2 tokens 148 / 139 / 139.
+// 32 experts, d 4096, 2 tokens 148 / 139 / 139.  The slices' sums take at most
+// SK_SLICE_BYTES (61 tokens at 4 slices: 36 MB).
 constexpr int SK_SPLIT_WGS = 640, SK_SPLIT_MAX = 4;
+
+long skinny_max_tokens(int E, int k) { return 64L * E / k > 16 ? 64L * E / k : 16; }
+
+int skinny_max_slices(int d) {
+    int s = 1;
+    while (s < SK_SPLIT_MAX && d / (2 * s) >= 1024) s *= 2;
+    return s;
+}
 
 int skinny_kslices(long T, long R, int E, int d, int f, int fs, int tt) {
     const long bm = 16 * tt;
     const long mt = (R < E ? R : E) > R / bm ? (R < E ? R : E) : R / bm;   // about the m-tiles there are
     const long wgs = mt * (f / (SK_COLS / 2)) + (T + bm - 1) / bm * (fs / (SK_COLS / 2));
     int s = 1;
-    while (s < SK_SPLIT_MAX && wgs * s < SK_SPLIT_WGS && d / (2 * s) >= 1024) s *= 2;
+    while (s < skinny_max_slices(d) && wgs * s < SK_SPLIT_WGS &&
+           16 * (size_t)s * ((size_t)R * f + (size_t)T * fs) <= SK_SLICE_BYTES)
+        s *= 2;
     return s;
 }
 
