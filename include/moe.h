@@ -455,7 +455,8 @@ moe_status moe_backward(const moe_shape *shape, const moe_bf16 *dY, const moe_bf
  *                     forward.
  *
  * Results are deterministic.  With one window (ring_rows >= T*k) they are
- * bitwise those of moe_forward / moe_backward; with several, Y, dX and the
+ * bitwise those of moe_forward / moe_backward (each with a workspace of at
+ * least its own byte count); with several, Y, dX and the
  * routed weight gradients differ only by fp32 summation order, and dZ and
  * dW_r are bitwise those of moe_backward.
  *   ring_rows >= 1 (MOE_EINVAL otherwise), < 2^31.

@@ -1157,15 +1157,20 @@ moe_status moe_forward_ring(const moe_shape *shape, const moe_bf16 *X, const moe
     const int nwin = ring_windows(*shape, ring_rows);
     int *coff = at<int>(ws, L.coff);
 
+    // one window holds every route: moe_forward's path, and its bits
+    const StageMarks none{nullptr, s};
     FwdPath path;
-    if (nwin == 1 && !dense_routing(*shape))
-        path = forward_path(*shape, save_for_backward, ws_bytes - L.fwd_total);
-    if (path.tt) {   // one window holds every route: the one-pass forward
-        MOE_TRY(small_forward(*shape, L, ws, X, weights, topk_w, plan, Y, path, StageMarks{nullptr, s}, s));
+    if (nwin == 1) path = forward_path(*shape, save_for_backward, ws_bytes - L.fwd_total);
+    if (path.tt) {
+        MOE_TRY(small_forward(*shape, L, ws, X, weights, topk_w, plan, Y, path, none, s));
         return MOE_OK;
     }
     MOE_TRY(launch_prep(plan->perm, plan->offsets, E, topk_w, k, T, at<int>(ws, L.rowidx),
                         at<float>(ws, L.wperm), at<uint16_t>(ws, L.zeros), s));
+    if (nwin == 1 && dense_routing(*shape)) {
+        MOE_TRY(dense_forward(*shape, L, ws, X, weights, plan, Y, save_for_backward != 0, path, none, s));
+        return MOE_OK;
+    }
     if (ring_folds(*shape, ring_rows)) {
         // per window: up/gate (H keeps w h) and the folded down product of
         // its experts; the first window processed also takes the shared

@@ -106,6 +106,34 @@ def test_ring_edge_shapes(w, ring_rows):
     compare_to_one_pass(full, ring, w, ring_rows)
 
 
+@pytest.mark.parametrize("save", [False, True])
+@pytest.mark.parametrize("w", [
+    Workload("small", T=40, d=512, E=5, k=5, f=512, f_s=256),             # streaming kernels (no backward)
+    Workload("small_slices", T=3, d=4352, E=3, k=3, f=256, f_s=512),      # K slices
+    Workload("parts", T=130, d=512, E=9, k=9, f=512, f_s=256),            # fp32 products, then their sum
+    Workload("parts_no_shared", T=70, d=256, E=3, k=3, f=1024),
+    Workload("folded_few", T=2000, d=2816, E=2, k=2, f=256, f_s=512),     # one folded product
+    Workload("folded_many", T=2900, d=2816, E=2, k=2, f=256),
+], ids=lambda w: w.name)
+def test_dense_one_window_bitwise(w, save):
+    """A ring of every route with dense routing: moe_forward's path whatever
+    the batch, with and without kept activations, and moe_backward's after it."""
+    inp = make_inputs(w.scaled(backward=save), 14)
+    R = w.T * w.k
+    say(f"[gpu] {w.name} T={w.T} d={w.d} E={w.E} f={w.f} f_s={w.f_s} save={save}")
+    full = DeviceLayer(w, inp, with_backward=save)
+    full.step()
+    for rows in (R, R + 5):
+        ring = DeviceLayer(w, inp, with_backward=save, ring_rows=rows)
+        ring.ws.fill_(0xA5)
+        ring.step()
+        torch.cuda.synchronize()
+        names = ("Y",) if not save else ("Y", "dX", "dZ", "dW_r", "dW_gate", "dW_up", "dW_down") + \
+            (SHARED if w.f_s else ())
+        for n in names:
+            assert torch.equal(getattr(full, n), getattr(ring, n)), f"{n} differs from the one-pass result"
+
+
 def test_ring_no_tokens():
     """An empty batch: one empty window; every weight gradient is zero."""
     w = Workload("no_tokens", T=0, d=256, E=8, k=2, f=256, f_s=256, backward=True)
