@@ -10,11 +10,11 @@
 
 #include "../../include/moe.h"
 #include "kernels.h"
+#include "rules.h"
 
 namespace {
 
 constexpr size_t ALIGN = 256;
-constexpr long DENSE_PARTS_MAX = 128;   // tiles of Y, half of the CUs
 
 size_t up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
@@ -46,18 +46,6 @@ struct Layout {
     long act_rows;             // rows of the per-route activation buffers
     int dg_parts;
 };
-
-// Dense routing on few token tiles: the folded down product has one workgroup
-// per 256 x 256 tile of Y and a K loop over every expert, so a short batch
-// leaves most CUs idle (200 tokens at d 7168: 28 workgroups of 288 K steps).
-// While it would fill at most half of them, the experts' products run as
-// tiles of their own into fp32 and a small kernel adds them in the same order
-// of experts.  Forward with 8 experts and a shared one (us), folded / in
-// parts: 200 tokens 706 / 387, 500 737 / 494, 1000 (112 workgroups) 913 / 846;
-// 1500 (168) 1185 / 1257, 2000 1386 / 1579: the fp32 traffic then costs more.
-bool dense_parts(const moe_shape &s) {
-    return s.k == s.E && s.T > 0 && (s.T + 255) / 256 * (s.d / 256) <= DENSE_PARTS_MAX;
-}
 
 // ring_rows < 0: per-route activations for all T*k routes; otherwise a ring
 // of ring_rows rows (bounded-memory execution).
@@ -387,7 +375,7 @@ FwdPath forward_path(const moe_shape &sh, int save, size_t room) {
     FwdPath p;
     p.tt = small_tiles(sh, save);
     if (p.tt) p.kslices = skinny_kslices((long)T, (long)R, (int)sh.E, (int)d, (int)f, (int)fs, p.tt);
-    p.parts = dense && (p.tt || dense_parts(sh));
+    p.parts = dense && (p.tt || dense_parts(sh.T, sh.d, sh.E, sh.k, sh.f, sh.f_shared));
     const size_t slices = p.kslices > 1 ? 8 * (size_t)p.kslices : 0, part = p.parts ? 4 : 0;
     p.at_s = up(std::max(slices * R * f, part * R * d));
     p.bytes = p.at_s + up(fs ? std::max(slices * T * fs, part * T * d) : 0);

@@ -1,0 +1,38 @@
+"""The library's dispatch rules (csrc/rules.h), compiled for the host, so that a
+test can state which path its shapes take."""
+import ctypes
+import functools
+import os
+import shutil
+import subprocess
+import tempfile
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2609_36070_amd", "csrc")
+
+SRC = """
+#include "rules.h"
+extern "C" {
+int t_dense_parts(long T, long d, long E, long k, long f, long fs) { return dense_parts(T, d, E, k, f, fs); }
+}
+"""
+
+HAVE_CXX = shutil.which("g++") is not None
+
+
+@functools.lru_cache(None)
+def _lib():
+    with tempfile.TemporaryDirectory() as tmp:
+        src, out = os.path.join(tmp, "rules.cpp"), os.path.join(tmp, "rules.so")
+        with open(src, "w") as fh:
+            fh.write(SRC)
+        subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, "-o", out, src], check=True)
+        return ctypes.CDLL(out)
+
+
+def _call(fn, *args):
+    return getattr(_lib(), fn)(*(ctypes.c_long(a) for a in args))
+
+
+def dense_parts(w):
+    """Dense routing: the experts' down products go to fp32 and are added, instead of one folded product."""
+    return bool(_call("t_dense_parts", w.T, w.d, w.E, w.k, w.f, w.f_s))

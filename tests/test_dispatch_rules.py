@@ -1,0 +1,32 @@
+"""The dispatch rules choose the faster side where both sides were measured
+(forward on one MI355X, us; CPU: the rules alone, compiled for the host)."""
+import pytest
+
+from paper_2609_36070_amd.workloads import Workload
+from tests import dispatch
+
+pytestmark = pytest.mark.skipif(not dispatch.HAVE_CXX, reason="needs a host compiler")
+
+
+@pytest.mark.parametrize("T,d,E,f,fs,folded,parts", [
+    # d, f, experts and a shared expert in the range; both ends of each
+    (100, 256, 16, 2048, 0, 670, 42), (8192, 256, 16, 2048, 0, 1194, 636), (30000, 256, 2, 256, 0, 48.6, 70.6),
+    (32768, 256, 8, 256, 0, 171, 257), (4099, 256, 8, 256, 0, 78.9, 49.4), (16384, 512, 8, 256, 0, 140, 222),
+    (8192, 1024, 8, 256, 0, 125, 203), (2048, 1024, 8, 1024, 0, 253, 128), (8192, 1024, 8, 1024, 0, 450, 481),
+    (4000, 2048, 2, 256, 0, 42.3, 62.2), (500, 2048, 8, 768, 0, 196, 87.5), (4000, 2048, 8, 768, 0, 321, 372),
+    (500, 2048, 16, 768, 1024, 405, 155), (4000, 2048, 16, 768, 1024, 706, 848), (2800, 2816, 2, 256, 512, 85, 131),
+    (1536, 4096, 8, 256, 0, 140, 205), (512, 4096, 16, 2048, 0, 988, 430), (1000, 7168, 2, 256, 0, 76, 91),
+    (200, 7168, 8, 2048, 2048, 706, 387), (500, 7168, 4, 2048, 2048, 493, 355),
+])
+def test_dense_down_products(T, d, E, f, fs, folded, parts):
+    w = Workload("dense", T=T, d=d, E=E, k=E, f=f, f_s=fs)
+    assert dispatch.dense_parts(w) == (parts < folded)
+
+
+def test_dense_down_products_bounds():
+    """Never for sparse routing, no tokens, or more tiles of Y than half of the CUs."""
+    dense = Workload("dense", T=200, d=7168, E=8, k=8, f=2048, f_s=2048)
+    assert dispatch.dense_parts(dense)
+    assert not dispatch.dense_parts(dense.scaled(k=7))
+    assert not dispatch.dense_parts(dense.scaled(T=0))
+    assert dispatch.dense_parts(dense.scaled(T=1024)) and not dispatch.dense_parts(dense.scaled(T=1025))

@@ -18,6 +18,7 @@ import torch
 from oracle import moe_oracle as O
 from paper_2609_36070_amd.layer import DeviceLayer
 from paper_2609_36070_amd.workloads import WORKLOADS, Workload, make_inputs
+from tests import dispatch
 from tests.parity import assert_close, check_route_and_plan, say, to_np, weights_dict
 
 pytestmark = pytest.mark.gpu
@@ -121,6 +122,7 @@ def test_dense_one_window_bitwise(w, save):
     inp = make_inputs(w.scaled(backward=save), 14)
     R = w.T * w.k
     say(f"[gpu] {w.name} T={w.T} d={w.d} E={w.E} f={w.f} f_s={w.f_s} save={save}")
+    assert w.T <= 64 or dispatch.dense_parts(w) == w.name.startswith("parts")
     full = DeviceLayer(w, inp, with_backward=save)
     full.step()
     for rows in (R, R + 5):

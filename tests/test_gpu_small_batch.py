@@ -10,6 +10,7 @@ import torch
 
 from paper_2609_36070_amd.layer import DeviceLayer
 from paper_2609_36070_amd.workloads import Workload, make_inputs
+from tests import dispatch
 from tests.parity import assert_close, to_np
 from tests.test_gpu_small import forward_parity
 
@@ -36,16 +37,20 @@ def test_small_batch_parity(w):
     forward_parity(w, seed=31)
 
 
-@pytest.mark.parametrize("w", [
-    # dense routing past the small batches: 121 tiles of Y (the experts' products
-    # summed from fp32) and 132 (the folded product), then the same with the
-    # activations kept
-    Workload("parts", T=2800, d=2816, E=2, k=2, f=256, f_s=512),
-    Workload("folded", T=2900, d=2816, E=2, k=2, f=256, f_s=512),
-    Workload("parts_train", T=130, d=512, E=9, k=9, f=256, backward=True),
-    Workload("folded_train", T=16700, d=512, E=2, k=2, f=256, f_s=256, backward=True),
-], ids=lambda w: w.name)
-def test_dense_down_products(w):
+@pytest.mark.parametrize("w,parts", [
+    # dense routing past the small batches: the experts' products summed from
+    # fp32 (in one round of tiles, in two), or the folded product (too much fp32
+    # traffic for what it saves: 121 tiles of Y; more than half of the CUs: 132),
+    # then the same with the activations kept
+    (Workload("parts", T=1500, d=1024, E=4, k=4, f=512, f_s=512), True),
+    (Workload("parts_rounds", T=1200, d=1024, E=16, k=16, f=256), True),
+    (Workload("folded_121", T=2800, d=2816, E=2, k=2, f=256, f_s=512), False),
+    (Workload("folded", T=2900, d=2816, E=2, k=2, f=256, f_s=512), False),
+    (Workload("parts_train", T=130, d=512, E=9, k=9, f=256, backward=True), True),
+    (Workload("folded_train", T=16700, d=512, E=2, k=2, f=256, f_s=256, backward=True), False),
+], ids=lambda v: v.name if isinstance(v, Workload) else "")
+def test_dense_down_products(w, parts):
+    assert dispatch.dense_parts(w) == parts
     forward_parity(w, seed=32)
 
 
