@@ -346,7 +346,7 @@ bool dense_routing(const moe_shape &sh) { return sh.k == sh.E; }
 int small_tiles(const moe_shape &sh, int save) {
     const int64_t R = sh.T * sh.k, lim = int64_t(1) << 32;   // 32-bit row offsets
     if (save || sh.T * sh.d >= lim || R * sh.f >= lim || sh.T * sh.f_shared >= lim) return 0;
-    return skinny_tiles((long)sh.T, (long)R, (int)sh.E);
+    return skinny_tiles(sh.T, sh.k, sh.E, sh.f, sh.f_shared);
 }
 
 // Rows of a ring's per-route activations.
@@ -399,7 +399,7 @@ size_t forward_bytes(const moe_shape &sh, int64_t ring_rows = -1) {
     size_t need = layout(sh.T);
     const int64_t tmax = ring_rows < 0 ? sh.T : std::min(sh.T, ring_rows / sh.k);
     auto with = [&](int64_t t, size_t scratch) { need = std::max(need, layout(t) + scratch + 2 * ALIGN); };
-    const int64_t ts = std::min(tmax, (int64_t)skinny_max_tokens((int)sh.E, (int)sh.k));
+    const int64_t ts = std::min(tmax, (int64_t)skinny_max_tokens(sh.E, sh.k));
     if (ts > 0 && skinny_max_slices((int)sh.d) > 1)
         with(ts, std::min(SK_SLICE_BYTES,
                           8 * (size_t)skinny_max_slices((int)sh.d) * (size_t)ts * (sh.k * sh.f + sh.f_shared)));

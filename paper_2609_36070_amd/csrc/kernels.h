@@ -155,13 +155,9 @@ struct SkinnyArgs {
                                        // Cfs [kslices][T][2 ldc_s] then hold their fp32 sums
     int nshared = 0, ntiles = 0;       // set by the launcher: tiles of the shared expert, in all
 };
-// 16-row tiles per workgroup for T tokens and R routes, 0: not a small batch.
-int skinny_tiles(long T, long R, int E);
 int skinny_kslices(long T, long R, int E, int d, int f, int fs, int tt);
-// Bounds of the two: tokens of a small batch, slices at hidden size d, and the
-// bytes that the slices' fp32 sums may take.
+// Its bounds: slices at hidden size d, and the bytes that their fp32 sums may take.
 constexpr size_t SK_SLICE_BYTES = size_t(48) << 20;
-long skinny_max_tokens(int E, int k);
 int skinny_max_slices(int d);
 hipError_t launch_skinny_up(const SkinnyArgs &g, int tt, hipStream_t st);
 hipError_t launch_skinny_down(const SkinnyArgs &g, int tt, hipStream_t st);

@@ -1,6 +1,36 @@
 // Which path a forward takes: rules on sizes alone, host code without HIP.
 #pragma once
 
+// Small batches (skinny.hip): 16-row tiles per workgroup, 0 for the tile GEMMs.
+//
+// 64-row tiles from 17 tokens up: more rows per pass over the weights beat
+// the smaller tiles' higher occupancy at every mean row count (128 experts, us
+// with 16 / 32 / 64 rows: 256 tokens 306 / 284 / 280, 512: 393 / 338 / 315);
+// up to 16 tokens no expert has more than 16 rows.
+//
+// Up to 64 rows per expert on average: there more experts take a second tile
+// and the tile GEMMs catch up.  (us here / there) 128 experts of 768, d 2048:
+// 512 tokens 276 / 333, 1000 330 / 353; 32 of 1536, d 4096: 100 tokens with a
+// hot expert 259 / 334, 250 336 / 341; 200 of 768, one expert per token: 8000
+// tokens 466 / 545, 12800 549 / 580.  The host sees the mean only, and an uneven
+// load moves the crossing down: with a router bias of std 2 it lies near 40 rows (128 experts: 32 rows 167 / 185,
+// 64 rows 237 / 216; 200 experts: 20 rows 182 / 201, 64 rows 325 / 271), and a
+// router collapsed onto 8 of 128 experts runs 512 tokens in 117 / 95.
+//
+// The shared expert's rows are all T tokens, re-reading its weights per 64 of
+// them: past the first 64 its products count up to the routed ones' bound, T f_s <= 64 E f.  200
+// experts of 768, one per token, and a shared one of 2048 (us here / there):
+// 4000 tokens (T f_s = 53 E f) 506 / 615, 8000 (107) 745 / 739, 12800 (171) 1003
+// / 892; of 1024: 8000 (53) 616 / 649, 12800 (85) 784 / 756; 32 of 1536 and one
+// of 2048: 1000 (42) 387 / 418, 2000 (83) 512 / 506.
+inline int skinny_tiles(long T, long k, long E, long f, long fs) {
+    if (T <= 0) return 0;
+    if (T <= 16) return 1;
+    return T * k <= 64 * E && (T <= 64 || T * fs <= 64 * E * f) ? 4 : 0;
+}
+// Tokens past which skinny_tiles is 0 for every f and fs.
+inline long skinny_max_tokens(long E, long k) { return 64 * E / k > 16 ? 64 * E / k : 16; }
+
 // Dense routing on few token tiles: the folded down product has one workgroup
 // per 256 x 256 tile of Y and a K loop over every expert, so a short batch
 // leaves most CUs idle (200 tokens at d 7168: 28 workgroups of 288 K steps).

@@ -32,6 +32,7 @@
 // segments), 8 waves on contiguous eighths of K (512 tokens, 128 experts: 351).
 #include "common.h"
 #include "kernels.h"
+#include "rules.h"
 
 namespace {
 
@@ -315,19 +316,6 @@ hipError_t launch_mode(SkinnyArgs g, int tt, hipStream_t st) {
 
 }  // namespace
 
-// 64-row tiles from 17 tokens up: more rows per pass over the weights beat
-// the smaller tiles' higher occupancy at every mean row count (128 experts, us
-// with 16 / 32 / 64 rows: 256 tokens 306 / 284 / 280, 512: 393 / 338 / 315);
-// up to 16 tokens no expert has more than 16 rows.  About 64 rows per expert
-// on average the tile GEMMs catch up, as more experts take a second tile (us
-// here / there: 32 experts, 150 tokens 285 / 361, 200: 309 / 359, 250: 373 /
-// 358; 128 experts, 512 tokens 297 / 354, 1000: 361 / 386).
-int skinny_tiles(long T, long R, int E) {
-    if (T <= 0) return 0;
-    if (T <= 16) return 1;
-    return R <= 64L * E ? 4 : 0;
-}
-
 // A CU's rate is bounded (its requests in flight), so a launch of one and a
 // bit workgroups per CU takes as long as two: 288 workgroups (8 experts and a
 // shared one of 2048 columns, d 7168) took 180 us at 61 tokens.  Below 640
@@ -337,8 +325,6 @@ int skinny_tiles(long T, long R, int E) {
 // 32 experts, d 4096, 2 tokens 148 / 139 / 139.  The slices' sums take at most
 // SK_SLICE_BYTES (61 tokens at 4 slices: 36 MB).
 constexpr int SK_SPLIT_WGS = 640, SK_SPLIT_MAX = 4;
-
-long skinny_max_tokens(int E, int k) { return 64L * E / k > 16 ? 64L * E / k : 16; }
 
 int skinny_max_slices(int d) {
     int s = 1;

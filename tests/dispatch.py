@@ -13,6 +13,7 @@ SRC = """
 #include "rules.h"
 extern "C" {
 int t_dense_parts(long T, long d, long E, long k, long f, long fs) { return dense_parts(T, d, E, k, f, fs); }
+int t_skinny_tiles(long T, long k, long E, long f, long fs) { return skinny_tiles(T, k, E, f, fs); }
 }
 """
 
@@ -31,6 +32,11 @@ def _lib():
 
 def _call(fn, *args):
     return getattr(_lib(), fn)(*(ctypes.c_long(a) for a in args))
+
+
+def small_tiles(w):
+    """A forward that keeps no activations: 16-row tiles per workgroup of the streaming kernels, 0 the tile GEMMs."""
+    return _call("t_skinny_tiles", w.T, w.k, w.E, w.f, w.f_s)
 
 
 def dense_parts(w):

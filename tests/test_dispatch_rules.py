@@ -23,6 +23,34 @@ def test_dense_down_products(T, d, E, f, fs, folded, parts):
     assert dispatch.dense_parts(w) == (parts < folded)
 
 
+@pytest.mark.parametrize("T,d,E,k,f,fs,small,tiles", [
+    # ordinary loads (router bias of std 0.5 or a hot expert), without and with a shared expert, then top 1 and top 2 of many
+    (512, 2048, 128, 8, 768, 0, 276, 333), (1000, 2048, 128, 8, 768, 0, 330, 353), (250, 4096, 32, 8, 1536, 0, 336, 341),
+    (512, 3072, 16, 2, 1024, 0, 108, 117), (256, 4096, 8, 2, 2048, 0, 141, 152),
+    (64, 4096, 32, 8, 1536, 2048, 284, 398), (128, 4096, 32, 8, 1536, 2048, 297, 409),
+    (1000, 4096, 32, 1, 1536, 2048, 387, 418), (2000, 4096, 32, 1, 1536, 2048, 512, 506),
+    (4000, 2048, 200, 1, 768, 2048, 506, 615), (8000, 2048, 200, 1, 768, 2048, 745, 739),
+    (12800, 2048, 200, 1, 768, 2048, 1003, 892), (8000, 2048, 200, 1, 768, 1024, 616, 649),
+    (12800, 2048, 200, 1, 768, 1024, 784, 756), (2000, 2048, 128, 2, 768, 1024, 313, 375),
+])
+def test_small_batches(T, d, E, k, f, fs, small, tiles):
+    w = Workload("small", T=T, d=d, E=E, k=k, f=f, f_s=fs)
+    assert bool(dispatch.small_tiles(w)) == (small < tiles)
+
+
+def test_small_batches_bounds():
+    w = Workload("small", T=128, d=256, E=4, k=2, f=512)
+    assert dispatch.small_tiles(w) == 4 and dispatch.small_tiles(w.scaled(T=129)) == 0      # 64 rows per expert
+    assert dispatch.small_tiles(w.scaled(T=16)) == 1 and dispatch.small_tiles(w.scaled(T=17)) == 4
+    assert dispatch.small_tiles(w.scaled(T=0)) == 0
+    dense = w.scaled(k=4)
+    assert dispatch.small_tiles(dense.scaled(T=64)) == 4 and dispatch.small_tiles(dense.scaled(T=65)) == 0
+    shared = Workload("shared", T=1024, d=256, E=64, k=1, f=256, f_s=1024)                   # T f_s = 64 E f
+    assert dispatch.small_tiles(shared) == 4 and dispatch.small_tiles(shared.scaled(T=1025)) == 0
+    wide = shared.scaled(f_s=32768)                                                          # one pass over its weights
+    assert dispatch.small_tiles(wide.scaled(T=64)) == 4 and dispatch.small_tiles(wide.scaled(T=65)) == 0
+
+
 def test_dense_down_products_bounds():
     """Never for sparse routing, no tokens, or more tiles of Y than half of the CUs."""
     dense = Workload("dense", T=200, d=7168, E=8, k=8, f=2048, f_s=2048)

@@ -2,7 +2,8 @@
 every output element against the oracle at the edges of their tiles.
 
 The rule is: not kept for a backward, and T <= 16 (16-row tiles) or at most 64
-routes per expert on average (64-row tiles).  Shapes lie on both sides of each
+routes per expert on average and a shared expert of bounded size (64-row
+tiles).  Shapes lie on both sides of each
 bound, with empty experts, experts of one row, of a whole tile and one row more.
 """
 import pytest
@@ -32,8 +33,12 @@ pytestmark = pytest.mark.gpu
     Workload("split_2", T=5, d=2304, E=4, k=2, f=256, f_s=256, bias_std=0.5),
     Workload("split_4_dense", T=40, d=4352, E=3, k=3, f=256, f_s=512),
     Workload("mean_64", T=128, d=256, E=4, k=2, f=512, f_s=512),      # R = 64 E exactly
+    Workload("mean_past", T=129, d=256, E=4, k=2, f=512, f_s=512),    # and past it
+    Workload("shared_at", T=1024, d=256, E=64, k=1, f=256, f_s=1024),     # the shared expert's rows at their bound
+    Workload("shared_past", T=1025, d=256, E=64, k=1, f=256, f_s=1024),   # and past it
 ], ids=lambda w: w.name)
 def test_small_batch_parity(w):
+    assert (dispatch.small_tiles(w) > 0) == (w.name not in ("dense_65", "mean_past", "shared_past"))
     forward_parity(w, seed=31)
 
 
