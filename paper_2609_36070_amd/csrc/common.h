@@ -134,13 +134,10 @@ DEV bool map_tile(int b, int tiles_m, int ntn, int &mt, int &nt) {
     return t >= 0 && map_group_tile(t / tpg, t % tpg, tiles_m, ntn, mt, nt);
 }
 
-// Workgroups of a launch whose tiles map_tile places (tiles_m or fewer m-tiles),
-// and with its last round split.
+// Workgroups of a launch whose tiles map_tile places (tiles_m or fewer
+// m-tiles), whole or with the last round split.
 inline long raster_grid(long tiles_m, int ntn) { return deal_grid(tiles_m * ntn, RASTER_CHUNK); }
-inline long split_grid(long tiles_m, int ntn) {
-    static_assert(4 * SPLIT_MAX <= 256, "the quarters fit the round's own slots");
-    return raster_grid(tiles_m, ntn);
-}
+static_assert(4 * SPLIT_MAX <= 256 && 8 * RASTER_CHUNK == 256, "the quarters fit the round's own slots");
 
 // The fused forward's raster: whole groups dealt to the XCDs, group g to XCD
 // g % 8, so that a tile and the tiles that wait for it can share an XCD.

@@ -1051,7 +1051,7 @@ hipError_t launch_mode(GemmArgs g, int tiles_m, int ntn, hipStream_t st, long gr
     const long tiles = (long)tiles_m * ntn;
     if (tiles <= 0) return hipSuccess;
     g.tiles_m = tiles_m;
-    const unsigned grid = (unsigned)(grid_blocks > 0 ? grid_blocks : split_grid(tiles_m, ntn));
+    const unsigned grid = (unsigned)(grid_blocks > 0 ? grid_blocks : raster_grid(tiles_m, ntn));
     if (g.offsets)
         gemm_kernel<MODE, true, SHAPE><<<dim3(grid), dim3(NTHREADS), 0, st>>>(g, g.a_rows, g.b_rows);
     else

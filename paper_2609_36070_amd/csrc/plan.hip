@@ -77,46 +77,16 @@ __global__ __launch_bounds__(1024) void plan_scan_kernel(int nb, int E,
                                                          int *__restrict__ err) {
     __shared__ int tot[MAXE];
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    if (nb <= 256) {
-        // up to 256 chunks: lane l holds chunks l + 64 m of each of the
-        // wave's experts (e = w + 16 q), all loaded before any scan
-        constexpr int QN = MAXE / 16;
-        int v[QN][4];
-        const int nm = (nb + 63) / 64;   // 64-chunk groups in use
-#pragma unroll
-        for (int q = 0; q < QN; ++q)
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                const int e = w + 16 * q, b = l + 64 * m;
-                v[q][m] = (e < E && m < nm && b < nb) ? blockcounts[(long)e * nb + b] : 0;
-            }
-#pragma unroll
-        for (int q = 0; q < QN; ++q) {
-            const int e = w + 16 * q;
-            if (e >= E) break;
-            int run = 0;
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                if (m >= nm) break;
-                const int b = l + 64 * m;
-                const int x = wave_incl_scan(v[q][m], l);
-                if (b < nb) blockbase[(long)e * nb + b] = run + x - v[q][m];
-                run += __shfl(x, 63, 64);
-            }
-            if (l == 0) tot[e] = run;
+    for (int e = w; e < E; e += 16) {
+        int run = 0;
+        for (int base = 0; base < nb; base += 64) {
+            const int b = base + l;
+            const int v = b < nb ? blockcounts[(long)e * nb + b] : 0;
+            const int x = wave_incl_scan(v, l);
+            if (b < nb) blockbase[(long)e * nb + b] = run + x - v;
+            run += __shfl(x, 63, 64);
         }
-    } else {
-        for (int e = w; e < E; e += 16) {
-            int run = 0;
-            for (int base = 0; base < nb; base += 64) {
-                const int b = base + l;
-                const int v = b < nb ? blockcounts[(long)e * nb + b] : 0;
-                const int x = wave_incl_scan(v, l);
-                if (b < nb) blockbase[(long)e * nb + b] = run + x - v;
-                run += __shfl(x, 63, 64);
-            }
-            if (l == 0) tot[e] = run;
-        }
+        if (l == 0) tot[e] = run;
     }
     __syncthreads();
     if (w == 0) {

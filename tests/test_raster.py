@@ -43,7 +43,7 @@ int main() {
             // with a short last round split: every tile once, whole or in its four quarters
             std::set<std::pair<int, int>> seen;
             long whole = 0;
-            for (long b = 0; b < split_grid(tm, ntn); ++b) {
+            for (long b = 0; b < raster_grid(tm, ntn); ++b) {
                 int q;
                 const int t = deal_tile_split((int)b, tm * ntn, q);
                 if (t < 0) continue;
