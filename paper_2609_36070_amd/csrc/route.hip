@@ -10,10 +10,11 @@
 // order, so the result is deterministic.  128 or more experts
 // (route_split_kernel, route_reduce_kernel): 128-token tiles over slices of
 // the d axis staged through LDS, partial tiles added in slice order by a
-// second kernel.  Up to 2048 tokens one launch on W_r as it lies
-// (route_direct_kernel).  The selection runs on groups of lanes per token.
+// second kernel.  Up to 2048 tokens one launch on W_r as it lies, if d is not
+// too long (route_direct_kernel).  The selection runs on groups of lanes per token.
 #include "common.h"
 #include "kernels.h"
+#include "rules.h"
 
 namespace {
 
@@ -614,18 +615,7 @@ __global__ __launch_bounds__(64 * rd_waves(EPAD)) void route_direct_kernel(
 
 }  // namespace
 
-int route_epad(int E) {
-    int p = 16;
-    while (p < E) p *= 2;
-    return p;
-}
-
-// Tokens up to which the one-launch router serves: it re-reads W_r per 16
-// tokens, and larger batches keep their logits' summation order.  us against
-// the other routers: 32 experts, d 4096: 1 token 8.7 / 16.2, 1000 11.7 / 19.3,
-// 2000 12.0 / 19.4; 128 experts, d 2048: 1 token 10.9 / 16.4, 1000 14.0 / 21.1;
-// 200 experts: 1000 tokens 23.5 / 33.4.
-constexpr int ROUTE_DIRECT_MAX = 2048;
+int route_epad(int E) { return (int)route_padded(E); }
 
 // Padded expert counts from which the split router runs.
 constexpr int ROUTE_SPLIT_MIN = 128;
@@ -649,8 +639,7 @@ hipError_t launch_route(const uint16_t *X, const uint16_t *W_r, const float *bia
                         int *topk_idx, float *topk_w, uint16_t *WrT, float *part, int T,
                         int d, int E, int k, hipStream_t st) {
     const int EPAD = route_epad(E);
-    // (its loads of several expert columns need them aligned in every row)
-    if (T > 0 && T <= ROUTE_DIRECT_MAX && E % (EPAD / 16 < 8 ? EPAD / 16 : 8) == 0) {
+    if (route_direct(T, d, E, k)) {
         const dim3 grid((unsigned)((T + 15) / 16)), block(64 * rd_waves(EPAD));
 #define ROUTE_DIRECT(EP) \
     route_direct_kernel<EP><<<grid, block, 0, st>>>(X, W_r, bias, logits, topk_idx, topk_w, T, d, E, k)

@@ -56,3 +56,37 @@ inline bool dense_parts(long T, long d, long E, long k, long f, long fs) {
     const long rounds = (E * nt + 255) / 256;
     return (E + (fs > 0)) * T * d < DENSE_PARTS_VALUES * f * (E - rounds);
 }
+
+// Experts padded to the routers' tiles.
+inline long route_padded(long E) {
+    long p = 16;
+    while (p < E) p *= 2;
+    return p;
+}
+
+// The one-launch router: it re-reads W_r per 16 tokens, so up to 2048 tokens,
+// and larger batches keep their logits' summation order.  Its loads of several
+// expert columns need them aligned in every row.
+//
+// Up to 64 experts at every d (us here / the other routers): 32 experts, d
+// 4096: 1 token 8.7 / 16.2, 1000 11.7 / 19.3, 2000 12.0 / 19.4; 64, d 16384:
+// 1 token 37 / 74, 2048 50 / 83.  Past that a wave's chain of steps is long (8
+// waves, 16 rows of W_r a lane in flight at 256) while the split router deals d
+// to 8 blocks, and the two cross between d 3584 and 6144, later for more routes
+// per token, which the split router's second launch selects on few CUs.
+// 128 experts, top 1: d 4608 16 tokens 15.5 / 15.0, 2048 20 / 23; d 5120 16.6 / 15.4;
+// top 8: d 5120 20 / 19, 500 tokens 22 / 24; d 7168 25 / 21, 29 / 26.  256 experts,
+// top 1: d 3584 20 / 21, 28 / 29; d 4096 2048 tokens 32 / 30; d 4608 36 / 30; top 8:
+// d 4608 30 / 30, 41 / 41; d 5120 740 tokens 34 / 40, 2048 45 / 41; d 7168 57 / 44;
+// top 16, d 5120: 55 / 62.  W_r, re-read per 16 tokens, counts too: top 8, d 5120,
+// 2048 tokens to 160 experts 38 / 42, 1600 to 200 40 / 42, to 256 44 / 43.  Over 3400 measured shapes at most 4 % (0.6 us) slower.
+constexpr long ROUTE_DIRECT_MAX = 2048, ROUTE_DIRECT_ROWS = 160 * 2048;
+
+inline bool route_direct(long T, long d, long E, long k) {
+    const long ep = route_padded(E), cols = ep / 16 < 8 ? ep / 16 : 8;
+    if (T <= 0 || T > ROUTE_DIRECT_MAX || E % cols) return false;
+    if (ep <= 64) return true;
+    if (ep == 128) return d <= (k >= 8 ? 5120 : 4608);
+    const long top = k >= 8 ? 4608 : k >= 4 ? 4096 : 3584;
+    return d <= top + (k >= 16 || (k >= 4 && T * E <= ROUTE_DIRECT_ROWS) ? 512 : 0);
+}

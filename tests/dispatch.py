@@ -14,6 +14,7 @@ SRC = """
 extern "C" {
 int t_dense_parts(long T, long d, long E, long k, long f, long fs) { return dense_parts(T, d, E, k, f, fs); }
 int t_skinny_tiles(long T, long k, long E, long f, long fs) { return skinny_tiles(T, k, E, f, fs); }
+int t_route_direct(long T, long d, long E, long k) { return route_direct(T, d, E, k); }
 }
 """
 
@@ -42,3 +43,8 @@ def small_tiles(w):
 def dense_parts(w):
     """Dense routing: the experts' down products go to fp32 and are added, instead of one folded product."""
     return bool(_call("t_dense_parts", w.T, w.d, w.E, w.k, w.f, w.f_s))
+
+
+def route_direct(T, d, E, k):
+    """The router runs as one launch on W_r as it lies."""
+    return bool(_call("t_route_direct", T, d, E, k))

@@ -58,3 +58,26 @@ def test_dense_down_products_bounds():
     assert not dispatch.dense_parts(dense.scaled(k=7))
     assert not dispatch.dense_parts(dense.scaled(T=0))
     assert dispatch.dense_parts(dense.scaled(T=1024)) and not dispatch.dense_parts(dense.scaled(T=1025))
+
+
+@pytest.mark.parametrize("T,d,E,k,direct,others", [
+    (1, 4096, 16, 8, 8, 12), (2048, 16384, 16, 8, 27, 37), (1, 16384, 64, 8, 37, 74), (2048, 7168, 64, 8, 26, 43),
+    (2048, 4608, 128, 8, 20.2, 25.1), (500, 5120, 128, 16, 26.6, 33.0), (1024, 5120, 128, 8, 21.4, 24.2),
+    (16, 5120, 128, 1, 16.6, 15.4), (16, 6144, 96, 8, 22.8, 20.6), (2048, 7168, 128, 8, 29.2, 26.3),
+    (1, 8192, 160, 8, 38.2, 33.8), (16, 4608, 160, 2, 25.5, 24.2), (1024, 5120, 200, 8, 34.2, 41.2),
+    (2048, 4608, 200, 8, 37.7, 41.7), (2048, 4608, 200, 2, 33.4, 31.4), (739, 7168, 200, 1, 46.9, 31.7),
+    (2048, 3584, 256, 1, 27.6, 29.1), (2048, 4096, 256, 1, 31.6, 29.5), (2048, 4608, 256, 1, 35.5, 29.6),
+    (16, 4096, 256, 4, 24.9, 25.1), (1024, 5120, 256, 8, 40.2, 41.6), (2048, 5120, 256, 8, 44.7, 41.7), (1600, 5120, 160, 8, 35.7, 42.1),
+    (2048, 5120, 256, 16, 54.9, 62.4), (512, 7168, 256, 8, 59, 43),
+])
+def test_routers(T, d, E, k, direct, others):
+    assert dispatch.route_direct(T, d, E, k) == (direct < others)
+
+
+def test_routers_bounds():
+    assert dispatch.route_direct(1, 256, 1, 1) and not dispatch.route_direct(0, 256, 1, 1)
+    assert dispatch.route_direct(2048, 256, 32, 8) and not dispatch.route_direct(2049, 256, 32, 8)
+    assert not dispatch.route_direct(64, 256, 100, 8)               # its columns do not align
+    for E, k, T, last in ((72, 7, 64, 4608), (128, 8, 2048, 5120), (136, 3, 64, 3584), (256, 4, 1280, 4608),
+                          (256, 4, 1281, 4096), (160, 15, 2048, 5120), (168, 15, 1951, 4608), (256, 16, 1281, 5120)):
+        assert dispatch.route_direct(T, last, E, k) and not dispatch.route_direct(T, last + 256, E, k)

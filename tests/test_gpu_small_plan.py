@@ -58,6 +58,8 @@ def test_plan_edges(T, k, E, bad):
     (300, 256, 96, 8), (2047, 512, 128, 16),                       # eight per lane
     (40, 768, 200, 10), (31, 256, 256, 1),                         # sixteen per lane
     (2049, 512, 32, 8), (1100, 512, 127, 8), (2100, 512, 128, 8),  # past its range: the other routers
+    (33, 5120, 128, 8), (33, 5376, 128, 8), (9, 7168, 200, 4),     # long rows of many experts: its last and theirs
+    (33, 4608, 72, 2), (33, 4864, 72, 2), (1280, 4608, 256, 4), (1281, 4608, 256, 4),
 ])
 def test_router_edges(T, d, E, k):
     say(f"[gpu] router T={T} d={d} E={E} k={k}")
