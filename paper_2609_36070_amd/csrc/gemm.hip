@@ -43,6 +43,7 @@
 // a fixed order: results are bitwise deterministic (§3.4 "Determinism").
 #include "common.h"
 #include "kernels.h"
+#include "rules.h"
 
 #include <type_traits>
 
@@ -1068,19 +1069,11 @@ static int mtiles(const GemmArgs &g, long rows, int groups) {
     return g.offsets ? (int)(rows / BM + (groups > 0 ? groups : 1)) : (int)((rows + BM - 1) / BM);
 }
 
-// The third stage of B pays while an expert's weights serve few m-tiles and
-// costs a little where they serve many (its loads then hit in L2 either way,
-// and more of them queue).  Forward, two / three stages (us), mean rows per
-// expert: 125: 394 / 369, 512 (128 experts): 906 / 878, 1000: 1315 / 1291,
-// 1024 (128 experts): 1570 / 1541, 2048: 2461 / 2453, 3000: 3580 / 3607, 4096:
-// 4752 / 4777.
-constexpr long DEEP_ROWS = 1024;
-
 template <int MODE>
 static hipError_t launch_rows(const GemmArgs &g, long rows, int groups, hipStream_t st) {
     const int tm = mtiles(g, rows, groups), ntn = g.N / (MODE == FWD_UP ? BN / 2 : BN);
-    return rows <= DEEP_ROWS * (groups > 0 ? groups : 1) ? launch_mode<MODE, DEEP>(g, tm, ntn, st)
-                                                        : launch_mode<MODE>(g, tm, ntn, st);
+    return deep_stages(g.K, rows, groups) ? launch_mode<MODE, DEEP>(g, tm, ntn, st)
+                                          : launch_mode<MODE>(g, tm, ntn, st);
 }
 
 hipError_t launch_gemm_fwd_up(const GemmArgs &g, long rows, int groups, hipStream_t st) {

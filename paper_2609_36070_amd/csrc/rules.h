@@ -79,7 +79,8 @@ inline long route_padded(long E) {
 // top 1: d 3584 20 / 21, 28 / 29; d 4096 2048 tokens 32 / 30; d 4608 36 / 30; top 8:
 // d 4608 30 / 30, 41 / 41; d 5120 740 tokens 34 / 40, 2048 45 / 41; d 7168 57 / 44;
 // top 16, d 5120: 55 / 62.  W_r, re-read per 16 tokens, counts too: top 8, d 5120,
-// 2048 tokens to 160 experts 38 / 42, 1600 to 200 40 / 42, to 256 44 / 43.  Over 3400 measured shapes at most 4 % (0.6 us) slower.
+// 2048 tokens to 160 experts 38 / 42, 1600 to 200 40 / 42, to 256 44 / 43.  Over
+// 3400 measured shapes at most 4 % (0.6 us) slower.
 constexpr long ROUTE_DIRECT_MAX = 2048, ROUTE_DIRECT_ROWS = 160 * 2048;
 
 inline bool route_direct(long T, long d, long E, long k) {
@@ -89,4 +90,25 @@ inline bool route_direct(long T, long d, long E, long k) {
     if (ep == 128) return d <= (k >= 8 ? 5120 : 4608);
     const long top = k >= 8 ? 4608 : k >= 4 ? 4096 : 3584;
     return d <= top + (k >= 16 || (k >= 4 && T * E <= ROUTE_DIRECT_ROWS) ? 512 : 0);
+}
+
+// The third LDS stage of B in a row product of `rows` rows over `groups` experts
+// (DEEP in gemm.hip) pays while an expert's weights serve few m-tiles and costs
+// a little where they serve many (its loads then hit in L2 either way, and more
+// of them queue).  Forward, two / three stages (us), mean rows per expert: 125:
+// 394 / 369, 512 (128 experts): 906 / 878, 1000: 1315 / 1291, 1024 (128 experts):
+// 1570 / 1541, 2048: 2461 / 2453, 3000: 3580 / 3607, 4096: 4752 / 4777.
+//
+// Short products have no K steps to hide it in: with 4 or 8 of 64 the loads
+// ahead are the whole product, and its tiles start later.  Forward that keeps
+// its activations, d = f, two / three stages (us): K 256, 128 experts: 16 rows
+// 34.3 / 35.3, 300 76.5 / 77.9; K 512: 16 rows 67.7 / 69.8, 100 79.4 / 81.1, 300
+// 164 / 161, 900 378 / 368; K 768: 16 rows 149 / 151, 300 326 / 311; K 1024, 64
+// experts: 16 rows 124 / 119, 300 267 / 253.
+constexpr long DEEP_ROWS = 1024, DEEP_K = 768, DEEP_SHORT_K = 512, DEEP_SHORT_ROWS = 200;
+
+inline bool deep_stages(long K, long rows, long groups) {
+    const long n = groups > 0 ? groups : 1;
+    if (rows > DEEP_ROWS * n) return false;
+    return K >= DEEP_K || (K >= DEEP_SHORT_K && rows >= DEEP_SHORT_ROWS * n);
 }

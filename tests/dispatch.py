@@ -15,6 +15,7 @@ extern "C" {
 int t_dense_parts(long T, long d, long E, long k, long f, long fs) { return dense_parts(T, d, E, k, f, fs); }
 int t_skinny_tiles(long T, long k, long E, long f, long fs) { return skinny_tiles(T, k, E, f, fs); }
 int t_route_direct(long T, long d, long E, long k) { return route_direct(T, d, E, k); }
+int t_deep_stages(long K, long rows, long groups) { return deep_stages(K, rows, groups); }
 }
 """
 
@@ -48,3 +49,8 @@ def dense_parts(w):
 def route_direct(T, d, E, k):
     """The router runs as one launch on W_r as it lies."""
     return bool(_call("t_route_direct", T, d, E, k))
+
+
+def deep_stages(K, rows, groups):
+    """A row product in a launch of its own holds three LDS stages of B instead of two."""
+    return bool(_call("t_deep_stages", K, rows, groups))

@@ -81,3 +81,23 @@ def test_routers_bounds():
     for E, k, T, last in ((72, 7, 64, 4608), (128, 8, 2048, 5120), (136, 3, 64, 3584), (256, 4, 1280, 4608),
                           (256, 4, 1281, 4096), (160, 15, 2048, 5120), (168, 15, 1951, 4608), (256, 16, 1281, 5120)):
         assert dispatch.route_direct(T, last, E, k) and not dispatch.route_direct(T, last + 256, E, k)
+
+
+@pytest.mark.parametrize("K,E,rows,two,three", [
+    # a forward with d = f = K, mean rows per expert
+    (256, 64, 16, 24.8, 25.4), (256, 128, 16, 34.3, 35.3), (256, 128, 300, 76.5, 77.9), (256, 64, 900, 125.4, 127.2),
+    (512, 64, 16, 44.7, 46.1), (512, 128, 100, 79.4, 81.1), (512, 128, 300, 163.9, 161.2), (512, 128, 900, 377.7, 368.2),
+    (768, 64, 300, 182.4, 173.5), (768, 128, 900, 675.8, 660.9), (1024, 64, 16, 124.1, 118.7),
+    (1024, 128, 300, 483.1, 474.1), (2048, 16, 100, 147.7, 136.7), (2048, 64, 900, 1699.6, 1664.8),
+    # longer products, from 125 to 4096 rows (8 experts of 2048, d 7168, and 128 of 768, d 2048)
+    (2048, 8, 125, 394, 369), (2048, 128, 512, 906, 878), (2048, 128, 1024, 1570, 1541), (2048, 8, 3000, 3580, 3607),
+    (2048, 8, 4096, 4752, 4777),
+])
+def test_third_stage(K, E, rows, two, three):
+    assert dispatch.deep_stages(K, rows * E, E) == (three < two)
+
+
+def test_third_stage_bounds():
+    assert dispatch.deep_stages(768, 1024 * 3, 3) and not dispatch.deep_stages(768, 1024 * 3 + 1, 3)
+    assert dispatch.deep_stages(512, 600, 3) and not dispatch.deep_stages(512, 599, 3)
+    assert not dispatch.deep_stages(256, 600, 3) and dispatch.deep_stages(768, 1, 0)
