@@ -374,7 +374,7 @@ FwdPath forward_path(const moe_shape &sh, int save, size_t room) {
     const bool dense = dense_routing(sh);
     FwdPath p;
     p.tt = small_tiles(sh, save);
-    if (p.tt) p.kslices = skinny_kslices((long)T, (long)R, (int)sh.E, (int)d, (int)f, (int)fs, p.tt);
+    if (p.tt) p.kslices = skinny_kslices(sh.T, sh.k, sh.E, sh.d, sh.f, sh.f_shared, p.tt);
     p.parts = dense && (p.tt || dense_parts(sh.T, sh.d, sh.E, sh.k, sh.f, sh.f_shared));
     const size_t slices = p.kslices > 1 ? 8 * (size_t)p.kslices : 0, part = p.parts ? 4 : 0;
     p.at_s = up(std::max(slices * R * f, part * R * d));
@@ -400,9 +400,9 @@ size_t forward_bytes(const moe_shape &sh, int64_t ring_rows = -1) {
     const int64_t tmax = ring_rows < 0 ? sh.T : std::min(sh.T, ring_rows / sh.k);
     auto with = [&](int64_t t, size_t scratch) { need = std::max(need, layout(t) + scratch + 2 * ALIGN); };
     const int64_t ts = std::min(tmax, (int64_t)skinny_max_tokens(sh.E, sh.k));
-    if (ts > 0 && skinny_max_slices((int)sh.d) > 1)
+    if (ts > 0 && skinny_max_slices(sh.d) > 1)
         with(ts, std::min(SK_SLICE_BYTES,
-                          8 * (size_t)skinny_max_slices((int)sh.d) * (size_t)ts * (sh.k * sh.f + sh.f_shared)));
+                          8 * (size_t)skinny_max_slices(sh.d) * (size_t)ts * (sh.k * sh.f + sh.f_shared)));
     const int64_t td = std::min(tmax, std::max(int64_t(64), DENSE_PARTS_MAX / (sh.d / 256) * 256));
     if (dense_routing(sh) && td > 0) with(td, 4 * (size_t)td * (size_t)(sh.k + (sh.f_shared > 0)) * sh.d);
     return need;

@@ -155,10 +155,6 @@ struct SkinnyArgs {
                                        // Cfs [kslices][T][2 ldc_s] then hold their fp32 sums
     int nshared = 0, ntiles = 0;       // set by the launcher: tiles of the shared expert, in all
 };
-int skinny_kslices(long T, long R, int E, int d, int f, int fs, int tt);
-// Its bounds: slices at hidden size d, and the bytes that their fp32 sums may take.
-constexpr size_t SK_SLICE_BYTES = size_t(48) << 20;
-int skinny_max_slices(int d);
 hipError_t launch_skinny_up(const SkinnyArgs &g, int tt, hipStream_t st);
 hipError_t launch_skinny_down(const SkinnyArgs &g, int tt, hipStream_t st);
 // Dense routing: Y from the fp32 down products (part [R][d] by plan row, part_s [T][d] or null).

@@ -1,6 +1,9 @@
 // Which path a forward takes: rules on sizes alone, host code without HIP.
 #pragma once
 
+#include <cmath>
+#include <cstddef>
+
 // Small batches (skinny.hip): 16-row tiles per workgroup, 0 for the tile GEMMs.
 //
 // 64-row tiles from 17 tokens up: more rows per pass over the weights beat
@@ -30,6 +33,55 @@ inline int skinny_tiles(long T, long k, long E, long f, long fs) {
 }
 // Tokens past which skinny_tiles is 0 for every f and fs.
 inline long skinny_max_tokens(long E, long k) { return 64 * E / k > 16 ? 64 * E / k : 16; }
+
+// Tiles of bm rows that R routes to E experts fill at most.
+inline long skinny_slots(long R, long E, long bm) { return (R < E ? R : E) + R / bm; }
+
+// K slices of a small batch's up/gate product: its workgroups (64 columns of f
+// each) run in rounds of the 256 CUs, so 288 of them (8 experts and a shared one
+// of 2048 columns) take as long as 512.  K is split over two or four where that
+// ends the launch earlier, if each slice keeps 1024 rows; the SwiGLU then moves to
+// a launch of its own (4 us), the slices are at most four or five rounds and their
+// sums take at most SK_SLICE_BYTES.
+//
+// Workgroups are counted for the experts that T balanced tokens reach, with a
+// tenth for the ones they reach beyond that.  Slices that just fit one round do
+// so only where the launch has no spare workgroups: those end at once and leave
+// their CU to a second one.
+//
+// Forward at 1 / 2 / 4 slices (us), by workgroups: 16, d 5120: 36 / - / 25; 64, d
+// 4096: 56 / 45 / 41; 96, d 2048: 32.5 / 30.2; 112, d 4096: 60 / 50 / 52; 128, d 2048:
+// 40 / 37, with spare ones 42 / 45; 148, d 4096: 62 / 65 / 56; 288, d 7168: 1 token
+// 186 / 169 / 160, 61 tokens 242 / 214 / 206; 344, d 7168: 186 / 175.  As many rounds
+// either way: 175, d 4096: 71 / 82 / 78; 210: 73 / 70 / 79; 256: 92 / 96 / 100; 444: 139 /
+// 144; 493, d 2048: 73 / 78.
+constexpr long SK_SPLIT_MAX = 4;
+constexpr size_t SK_SLICE_BYTES = size_t(48) << 20;
+
+inline long skinny_max_slices(long d) {
+    long s = 1;
+    while (s < SK_SPLIT_MAX && d / (2 * s) >= 1024) s *= 2;
+    return s;
+}
+
+inline int skinny_kslices(long T, long k, long E, long d, long f, long fs, long tt) {
+    const long R = T * k, bm = 16 * tt, shared = (T + bm - 1) / bm * (fs / 64);
+    double reached = E * (1.0 - std::pow(1.0 - (double)k / E, (double)T));
+    if (reached < R / bm) reached = (double)(R / bm);
+    const long wgs = (long)std::ceil(reached * (f / 64) - 1e-6) + shared;
+    const long grid = skinny_slots(R, E, bm) * (f / 64) + shared;
+    long best = 1, rounds = (wgs + 255) / 256;        // of `best` slices each
+    for (long s = 2; s <= skinny_max_slices(d); s *= 2) {
+        const long n = wgs * s;
+        if (wgs > (s == 2 ? 512 : 320) || 8 * (size_t)s * ((size_t)R * f + (size_t)T * fs) > SK_SLICE_BYTES) break;
+        const long r = n <= 252 || (n <= 256 && grid * s <= 256) ? 1 : (n + n / 10 + 255) / 256;
+        if (r * best < rounds * s) {
+            best = s;
+            rounds = r;
+        }
+    }
+    return (int)best;
+}
 
 // Dense routing on few token tiles: the folded down product has one workgroup
 // per 256 x 256 tile of Y and a K loop over every expert, so a short batch

@@ -303,7 +303,7 @@ __global__ __launch_bounds__(256) void dense_sum_kernel(const float *__restrict_
 template <int MODE>
 hipError_t launch_mode(SkinnyArgs g, int tt, hipStream_t st) {
     const int ncols = MODE == SK_UP || MODE == SK_UP_PART ? SK_COLS / 2 : SK_COLS, bm = 16 * tt;
-    const long slots = (g.R < g.E ? g.R : g.E) + g.R / bm;   // >= sum of ceil(rows / bm)
+    const long slots = skinny_slots(g.R, g.E, bm);
     g.nshared = g.Ns > 0 ? (g.T + bm - 1) / bm * (g.Ns / ncols) : 0;
     g.ntiles = (int)(g.nshared + slots * (g.N / ncols));
     const long grid = (long)g.ntiles * (MODE == SK_UP_PART ? g.kslices : 1);
@@ -315,33 +315,6 @@ hipError_t launch_mode(SkinnyArgs g, int tt, hipStream_t st) {
 }
 
 }  // namespace
-
-// A CU's rate is bounded (its requests in flight), so a launch of one and a
-// bit workgroups per CU takes as long as two: 288 workgroups (8 experts and a
-// shared one of 2048 columns, d 7168) took 180 us at 61 tokens.  Below 640
-// workgroups (2.5 per CU) K is split over two or four, if each keeps 1024
-// rows, and the SwiGLU moves to a small launch: 137 + 8 us.  Whole forward at
-// 1 / 2 / 4 slices (us): 61 tokens 267 / 241 / 232, 1 token 212 / 195 / 182;
-// 32 experts, d 4096, 2 tokens 148 / 139 / 139.  The slices' sums take at most
-// SK_SLICE_BYTES (61 tokens at 4 slices: 36 MB).
-constexpr int SK_SPLIT_WGS = 640, SK_SPLIT_MAX = 4;
-
-int skinny_max_slices(int d) {
-    int s = 1;
-    while (s < SK_SPLIT_MAX && d / (2 * s) >= 1024) s *= 2;
-    return s;
-}
-
-int skinny_kslices(long T, long R, int E, int d, int f, int fs, int tt) {
-    const long bm = 16 * tt;
-    const long mt = (R < E ? R : E) > R / bm ? (R < E ? R : E) : R / bm;   // about the m-tiles there are
-    const long wgs = mt * (f / (SK_COLS / 2)) + (T + bm - 1) / bm * (fs / (SK_COLS / 2));
-    int s = 1;
-    while (s < skinny_max_slices(d) && wgs * s < SK_SPLIT_WGS &&
-           16 * (size_t)s * ((size_t)R * f + (size_t)T * fs) <= SK_SLICE_BYTES)
-        s *= 2;
-    return s;
-}
 
 hipError_t launch_skinny_up(const SkinnyArgs &g, int tt, hipStream_t st) {
     if (g.kslices <= 1) return launch_mode<SK_UP>(g, tt, st);

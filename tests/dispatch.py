@@ -14,6 +14,8 @@ SRC = """
 extern "C" {
 int t_dense_parts(long T, long d, long E, long k, long f, long fs) { return dense_parts(T, d, E, k, f, fs); }
 int t_skinny_tiles(long T, long k, long E, long f, long fs) { return skinny_tiles(T, k, E, f, fs); }
+int t_skinny_kslices(long T, long k, long E, long d, long f, long fs) {
+    return skinny_kslices(T, k, E, d, f, fs, skinny_tiles(T, k, E, f, fs)); }
 int t_route_direct(long T, long d, long E, long k) { return route_direct(T, d, E, k); }
 int t_deep_stages(long K, long rows, long groups) { return deep_stages(K, rows, groups); }
 }
@@ -39,6 +41,11 @@ def _call(fn, *args):
 def small_tiles(w):
     """A forward that keeps no activations: 16-row tiles per workgroup of the streaming kernels, 0 the tile GEMMs."""
     return _call("t_skinny_tiles", w.T, w.k, w.E, w.f, w.f_s)
+
+
+def kslices(w):
+    """Workgroups of a small batch that share an up/gate tile's K."""
+    return _call("t_skinny_kslices", w.T, w.k, w.E, w.d, w.f, w.f_s)
 
 
 def dense_parts(w):

@@ -51,6 +51,36 @@ def test_small_batches_bounds():
     assert dispatch.small_tiles(wide.scaled(T=64)) == 4 and dispatch.small_tiles(wide.scaled(T=65)) == 0
 
 
+@pytest.mark.parametrize("T,d,E,k,f,fs,us", [
+    # us with 1, 2 (and 4) slices; batches whose tokens reach other experts each time
+    (1, 2048, 128, 8, 768, 0, (32.5, 30.2)), (2, 2048, 128, 8, 768, 0, (37.9, 41.6)), (6, 2048, 128, 8, 768, 0, (74, 78.6)),
+    (2, 4096, 32, 8, 1536, 0, (125.5, 117)), (3, 4096, 32, 8, 1536, 0, (139, 144)),
+    (1, 7168, 8, 8, 2048, 2048, (186, 169, 160)), (61, 7168, 8, 8, 2048, 2048, (242, 214, 206)),
+    (24, 2048, 8, 2, 1024, 0, (40.5, 36.9)), (61, 2048, 8, 2, 1024, 0, (44.1, 45.6)),
+    (1, 4096, 8, 2, 2048, 0, (56, 45, 41)), (2, 4096, 8, 2, 2048, 0, (60, 50, 52)), (3, 4096, 8, 2, 2048, 0, (62, 65, 56)),
+    (4, 4096, 8, 2, 2048, 0, (70, 82, 76)), (24, 4096, 8, 2, 2048, 0, (88, 92, 94)), (61, 4096, 8, 2, 2048, 0, (93, 96, 101)),
+    (8, 7168, 64, 8, 512, 512, (186, 175)), (16, 7168, 64, 8, 512, 512, (230, 234)),
+    (2, 5120, 200, 2, 512, 0, (56, 40, 33)), (24, 5120, 200, 2, 512, 0, (138, 129)),
+    (16, 3072, 8, 2, 2048, 0, (65.8, 70)), (4, 2048, 16, 16, 1024, 1024, (65.7, 63)),
+])
+def test_small_batch_slices(T, d, E, k, f, fs, us):
+    w = Workload("small", T=T, d=d, E=E, k=k, f=f, f_s=fs)
+    assert dispatch.kslices(w) == 2 ** us.index(min(us))
+
+
+def test_small_batch_slices_bounds():
+    w = Workload("small", T=1, d=2048, E=8, k=1, f=256)
+    assert dispatch.kslices(w) == 2 and dispatch.kslices(w.scaled(d=4096)) == 4
+    assert dispatch.kslices(w.scaled(d=1792)) == 1 and dispatch.kslices(w.scaled(d=3840)) == 2   # 1024 rows per slice
+    one = Workload("one", T=1, d=2048, E=1, k=1, f=256)
+    assert dispatch.kslices(one.scaled(f=64 * 128)) == 2      # 128 workgroups: one round of slices
+    assert dispatch.kslices(one.scaled(f=64 * 132)) == 1      # two rounds of slices
+    assert dispatch.kslices(one.scaled(f=64 * 260)) == 2      # two rounds, three of slices
+    assert dispatch.kslices(one.scaled(f=64 * 516)) == 1
+    for f, slices in ((64 * 288, 4), (64 * 320, 2), (64 * 344, 2), (64 * 388, 1)):    # as many rounds at two and at four
+        assert dispatch.kslices(one.scaled(d=4096, f=f)) == slices
+
+
 def test_dense_down_products_bounds():
     """Never for sparse routing, no tokens, or more tiles of Y than half of the CUs."""
     dense = Workload("dense", T=200, d=7168, E=8, k=8, f=2048, f_s=2048)
