@@ -2,7 +2,8 @@
 
 The fused launch runs the same tile code as the separate launches and adds
 the combine in the same order, so every output must equal moe_forward's
-bitwise; it is also checked against the oracle.  The error word must stay 0
+bitwise; it is also checked against the oracle.  Which shapes run that launch is
+asserted for each (persistent below).  The error word must stay 0
 (bit 1 would mean a dependency wait gave up).
 """
 import numpy as np
@@ -13,12 +14,19 @@ from oracle import moe_oracle as O
 from paper_2609_36070_amd import binding as B
 from paper_2609_36070_amd.layer import DeviceLayer
 from paper_2609_36070_amd.workloads import WORKLOADS, Workload, make_inputs
+from tests import dispatch
 from tests.parity import assert_close, check_route_and_plan, say, to_np, weights_dict
 
 pytestmark = pytest.mark.gpu
 
 RAGGED_TRAIN = Workload("ragged_train", T=1000, d=512, E=6, k=2, f=512, f_s=256, bias_std=0.5,
                         backward=True)
+
+
+def persistent(w):
+    """Whether the fused entry point runs its one launch: small batches that keep
+    no activations and dense products in parts take moe_forward's launches."""
+    return not (dispatch.small_tiles(w) and not w.backward) and not dispatch.dense_parts(w)
 
 
 def regions(L, w):
@@ -63,10 +71,11 @@ def assert_bitwise(ref, got):
 
 
 @pytest.mark.parametrize("w", [RAGGED_TRAIN,
-                               Workload("dense_shared_train", T=700, d=512, E=4, k=4, f=512,
+                               Workload("dense_shared_train", T=1111, d=2048, E=6, k=6, f=256,
                                         f_s=256, bias_std=0.5, backward=True)],
                          ids=lambda w: w.name)
 def test_fused_training_layer(w):
+    assert persistent(w)
     L, inp, ref, got = run_both(w, 21)
     assert_bitwise(ref, got)
     Zo, idx_g = check_route_and_plan(L, inp, w)
@@ -82,15 +91,31 @@ def test_fused_training_layer(w):
 
 
 @pytest.mark.parametrize("w", [
-    Workload("one_token", T=1, d=256, E=8, k=3, f=256, f_s=256),
-    Workload("k_equals_E", T=300, d=256, E=4, k=4, f=512, bias_std=0.5),
-    Workload("empty_experts", T=40, d=256, E=64, k=1, f=256, bias_std=3.0),
+    Workload("one_token", T=1, d=256, E=8, k=3, f=256, f_s=256, backward=True),
+    Workload("k_equals_E", T=2900, d=2816, E=2, k=2, f=256, bias_std=0.5),
+    Workload("empty_experts", T=40, d=256, E=64, k=1, f=256, bias_std=3.0, backward=True),
     Workload("many_tiles", T=700, d=768, E=3, k=2, f=768),
     Workload("no_shared_k16", T=600, d=256, E=32, k=16, f=256, bias_std=0.5),
-    Workload("max_experts", T=2000, d=256, E=256, k=4, f=256, f_s=512, bias_std=1.0),
-    Workload("dense_shared", T=555, d=768, E=6, k=6, f=256, f_s=512, bias_std=0.5),
+    Workload("max_experts", T=5000, d=256, E=256, k=4, f=256, f_s=512, bias_std=1.0),
+    Workload("dense_shared", T=1555, d=2048, E=2, k=2, f=256, f_s=512, bias_std=0.5),
 ], ids=lambda w: w.name)
 def test_fused_edge_shapes(w):
+    assert persistent(w)
+    check_forward(w)
+
+
+@pytest.mark.parametrize("w", [
+    Workload("one_token", T=1, d=256, E=8, k=3, f=256, f_s=256),
+    Workload("k_equals_E", T=300, d=256, E=4, k=4, f=512, bias_std=0.5),
+    Workload("dense_shared", T=555, d=768, E=6, k=6, f=256, f_s=512, bias_std=0.5),
+    Workload("dense_train", T=700, d=512, E=4, k=4, f=512, f_s=256, bias_std=0.5, backward=True),
+], ids=lambda w: w.name)
+def test_fused_other_launches(w):
+    assert not persistent(w)
+    check_forward(w)
+
+
+def check_forward(w):
     L, inp, ref, got = run_both(w, 22)
     assert_bitwise(ref, got)
     Zo, idx_g = check_route_and_plan(L, inp, w)
@@ -141,6 +166,7 @@ def test_fused_full_size(name):
     the full-size parity tests check against the oracle), plus sampled
     token rows of Y against the oracle."""
     w = WORKLOADS[name]
+    assert persistent(w)
     L, inp, ref, got = run_both(w, 0)
     assert_bitwise(ref, got)
     Zo, idx_g = check_route_and_plan(L, inp, w)
