@@ -1,5 +1,5 @@
-"""The library's dispatch rules (csrc/rules.h), compiled for the host, so that a
-test can state which path its shapes take."""
+"""The library's dispatch rules (csrc/rules.h, csrc/raster.h), compiled for the
+host, so that a test can state which path its shapes take."""
 import ctypes
 import functools
 import os
@@ -10,8 +10,17 @@ import tempfile
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2609_36070_amd", "csrc")
 
 SRC = """
+#include <algorithm>
 #include "rules.h"
+using std::min;
+#define DEV static inline
+#include "raster.h"
 extern "C" {
+int t_quartered(long n) {
+    int q, most = 0;
+    for (int b = 0; b < deal_grid(n, RASTER_CHUNK); ++b) most |= deal_tile_split(b, (int)n, q) >= 0 ? 1 << (q >= 0) : 0;
+    return most;
+}
 int t_dense_parts(long T, long d, long E, long k, long f, long fs) { return dense_parts(T, d, E, k, f, fs); }
 int t_skinny_tiles(long T, long k, long E, long f, long fs) { return skinny_tiles(T, k, E, f, fs); }
 int t_skinny_kslices(long T, long k, long E, long d, long f, long fs) {
@@ -61,3 +70,10 @@ def route_direct(T, d, E, k):
 def deep_stages(K, rows, groups):
     """A row product in a launch of its own holds three LDS stages of B instead of two."""
     return bool(_call("t_deep_stages", K, rows, groups))
+
+
+def tile_shapes(tiles, K, rows, groups):
+    """The tile shapes that a row product of `tiles` tiles runs in a launch of its own."""
+    got = _call("t_quartered", tiles)
+    whole = "three" if deep_stages(K, rows, groups) else "two"
+    return ({whole} if got & 1 else set()) | ({"quarters"} if got & 2 else set())
