@@ -177,6 +177,10 @@ typedef struct {
  * recorded on the stream just before stage i is enqueued and ev[n] after the
  * last stage, so the elapsed time between ev[i] and ev[i+1] is stage i.
  * Stages that do not apply (no shared expert) still record their events.
+ * Where one launch does the work of several stages its time is that of the
+ * first of them: a small batch's forward has no prologue and runs the shared
+ * expert in stages 1 and 3 with the routed ones; larger batches with dense
+ * routing have the whole down product and the sum into Y in stage 3.
  *   forward  (n = 6): 0 plan-order prologue, 1 routed up/gate + SwiGLU,
  *                     2 shared up/gate + SwiGLU, 3 routed down, 4 shared down,
  *                     5 combine.
@@ -211,8 +215,9 @@ moe_status moe_workspace_region(const moe_shape *shape, int with_backward,
  *   topk_idx [T, k] int32 out: the k largest logits, ties to the lower
  *            expert id, listed in ascending expert id.
  *   topk_w  [T, k] fp32 out: exp(Z_te) / sum_{e' in S_t} exp(Z_te').
- * Uses the workspace for a transposed copy of W_r and, with 128 or more
- * experts, for fp32 partial logits of slices of the d axis (added in slice
+ * Larger batches and long rows of many experts use the workspace for a
+ * transposed copy of W_r and, with more than 64 experts, for fp32 partial
+ * logits of slices of the d axis (added in slice
  * order, so the logits are deterministic). */
 moe_status moe_route(const moe_shape *shape, const moe_bf16 *X, const moe_bf16 *W_r,
                      const float *bias, float *logits, int32_t *topk_idx, float *topk_w,
@@ -387,12 +392,16 @@ moe_status moe_dispatch(const moe_shape *shape, const moe_bf16 *X,
  *   id of w * f_e(x_t), accumulated in fp32 and rounded once.
  *   save_for_backward: keep A and B (gate/up pre-activations) in ws.
  * Dense routing (k == E; each token's k ids are then 0 .. E-1): the token's
- * route to expert e is plan row offsets[e] + t, so the combine is one
+ * route to expert e is plan row offsets[e] + t, so the combine is a
  * contraction over the experts' intermediate columns in ascending expert id
  * followed by the shared expert's: Y[t] = sum_e (w h_e[t]) W_down[e] +
- * h_s[t] Wd_s in one fp32 accumulator (w h rounded to bf16), rounded once.
- * The same holds for dX in moe_backward (routed terms in ascending expert
- * id, then the shared expert, then dZ[t] W_r^T, one fp32 accumulator). */
+ * h_s[t] Wd_s (w h rounded to bf16), rounded once.  The sum is one fp32
+ * accumulator, or, for small and short batches, each expert's fp32 product
+ * added in that order.  Which of them runs depends on the sizes and on whether
+ * the workspace has room for the products (moe_workspace_bytes does), so a
+ * token's last bits can differ between batches of different sizes.
+ * dX in moe_backward is summed likewise in one fp32 accumulator (routed terms
+ * in ascending expert id, then the shared expert, then dZ[t] W_r^T). */
 moe_status moe_forward(const moe_shape *shape, const moe_bf16 *X, const moe_weights *weights,
                        const int32_t *topk_idx, const float *topk_w,
                        const moe_plan_bufs *plan, moe_bf16 *Y, int save_for_backward,
@@ -408,6 +417,8 @@ moe_status moe_forward(const moe_shape *shape, const moe_bf16 *X, const moe_weig
  * of its rows is done; a token block's combine starts when the down tiles
  * holding all of its routes are done, so the combine overlaps the last down
  * tiles instead of following them.
+ * Small batches and short dense ones, which leave nothing to overlap, run
+ * moe_forward's launches instead.
  * Same arguments, workspace and results as moe_forward, bitwise (each tile
  * runs the same code, the combine adds in the same order); A and B are kept
  * when save_for_backward = 1, so moe_backward can follow.  Every wait is

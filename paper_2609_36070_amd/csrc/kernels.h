@@ -37,7 +37,7 @@ struct GemmArgs {
     long c_estride = 0;
     const uint16_t *E1 = nullptr, *E2 = nullptr;  // BWD_DGRAD: saved A, B
     const float *rowscale = nullptr;              // BWD_DGRAD: router weight per row
-    float *dgpart = nullptr;
+    float *dgpart = nullptr;           // BWD_DGRAD: <dh', h> partial per row and 128 columns
     int dg_ld = 0;
     int accumulate = 0;                // WGRAD: add to Cf instead of overwriting it
     int tiles_m = 0;                   // set by the launcher: m-tile slots of the raster
