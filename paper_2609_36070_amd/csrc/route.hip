@@ -7,7 +7,7 @@
 // each wave accumulates 16 MT x EPAD partial logits with
 // v_mfma_f32_16x16x32_bf16 reading X rows straight from HBM and the
 // transposed router W_r^T from L2.  The partial sums are added in wave
-// order, so the result is deterministic.  128 or more experts
+// order, so the result is deterministic.  More than 64 experts
 // (route_split_kernel, route_reduce_kernel): 128-token tiles over slices of
 // the d axis staged through LDS, partial tiles added in slice order by a
 // second kernel.  Up to 2048 tokens one launch on W_r as it lies, if d is not

@@ -16,16 +16,17 @@
 // 512 tokens 276 / 333, 1000 330 / 353; 32 of 1536, d 4096: 100 tokens with a
 // hot expert 259 / 334, 250 336 / 341; 200 of 768, one expert per token: 8000
 // tokens 466 / 545, 12800 549 / 580.  The host sees the mean only, and an uneven
-// load moves the crossing down: with a router bias of std 2 it lies near 40 rows (128 experts: 32 rows 167 / 185,
-// 64 rows 237 / 216; 200 experts: 20 rows 182 / 201, 64 rows 325 / 271), and a
-// router collapsed onto 8 of 128 experts runs 512 tokens in 117 / 95.
+// load moves the crossing down: with a router bias of std 2 it lies near 40 rows
+// (128 experts: 32 rows 167 / 185, 64 rows 237 / 216; 200 experts: 20 rows 182 /
+// 201, 64 rows 325 / 271), and a router collapsed onto 8 of 128 experts runs 512
+// tokens in 117 / 95.
 //
 // The shared expert's rows are all T tokens, re-reading its weights per 64 of
-// them: past the first 64 its products count up to the routed ones' bound, T f_s <= 64 E f.  200
-// experts of 768, one per token, and a shared one of 2048 (us here / there):
-// 4000 tokens (T f_s = 53 E f) 506 / 615, 8000 (107) 745 / 739, 12800 (171) 1003
-// / 892; of 1024: 8000 (53) 616 / 649, 12800 (85) 784 / 756; 32 of 1536 and one
-// of 2048: 1000 (42) 387 / 418, 2000 (83) 512 / 506.
+// them: past the first 64 its products count up to the routed ones' bound, T f_s
+// <= 64 E f.  200 experts of 768, one per token, and a shared one of 2048 (us
+// here / there): 4000 tokens (T f_s = 53 E f) 506 / 615, 8000 (107) 745 / 739,
+// 12800 (171) 1003 / 892; of 1024: 8000 (53) 616 / 649, 12800 (85) 784 / 756; 32 of
+// 1536 and one of 2048: 1000 (42) 387 / 418, 2000 (83) 512 / 506.
 inline int skinny_tiles(long T, long k, long E, long f, long fs) {
     if (T <= 0) return 0;
     if (T <= 16) return 1;
