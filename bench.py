@@ -94,7 +94,7 @@ def stage_flops(w):
 
 
 # sources the BF16 GEMM kernels are compiled from (device code and helpers)
-GEMM_SOURCES = ("gemm.hip", "common.h", "raster.h", "rules.h")
+GEMM_SOURCES = ("gemm.hip", "common.h", "raster.h")
 
 
 def source_sha256():

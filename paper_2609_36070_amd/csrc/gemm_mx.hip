@@ -35,6 +35,7 @@
 // to LDS by the same direct loads, one stage ahead, together with the tiles.
 #include "common.h"
 #include "kernels.h"
+#include "rules.h"
 #include "mx_common.h"
 
 #define LDSP __attribute__((address_space(3)))
@@ -42,7 +43,7 @@
 namespace {
 
 // Epilogue stores go past L2, which holds the operand panels (their readers
-// are later launches).  48000 rows, 32 experts, d 4096, f 1536, us: up with
+// are later launches; mx_keep_l2 has the exception).  48000 rows, 32 experts, d 4096, f 1536, us: up with
 // kept activations 844 -> 816, down 434 -> 411, dgrad 696 -> 673, dX 760 -> 737.
 DEV void st_nt(void *p, u32x4_t v) { __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t *>(p)); }
 DEV void st_nt(float *p, const f32x8 &v) {
@@ -399,8 +400,13 @@ __global__ __launch_bounds__(NTHREADS, 1) void gemm_mx_kernel(MxGemmArgs g, cons
                         if (g.Sa) {   // pre-activations for the backward, fp32
                             float *sa = g.Sa + (long)p * g.N + fcol0 + c;
                             float *sb = g.Sb + (long)p * g.N + fcol0 + c;
-                            st_nt(sa, a);
-                            st_nt(sb, b);
+                            if (g.keep_l2) {
+                                st_f32x8(sa, a);
+                                st_f32x8(sb, b);
+                            } else {
+                                st_nt(sa, a);
+                                st_nt(sb, b);
+                            }
                         }
                     }
                 }
@@ -562,7 +568,8 @@ int mx_mtiles(long rows, int groups) { return (int)(rows / BM + (groups > 0 ? gr
 
 }  // namespace
 
-hipError_t launch_gemm_mx_up(const MxGemmArgs &g, long rows, int groups, hipStream_t st) {
+hipError_t launch_gemm_mx_up(MxGemmArgs g, long rows, int groups, hipStream_t st) {
+    g.keep_l2 = mx_keep_l2(rows, groups, g.K, g.N);
     return launch_mx_mode<MX_UP>(g, mx_mtiles(rows, groups), g.N / (BN / 2), st);
 }
 hipError_t launch_gemm_mx_down(const MxGemmArgs &g, long rows, int groups, hipStream_t st) {

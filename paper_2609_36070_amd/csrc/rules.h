@@ -165,3 +165,17 @@ inline bool deep_stages(long K, long rows, long groups) {
     if (rows > DEEP_ROWS * n) return false;
     return K >= DEEP_K || (K >= DEEP_SHORT_K && rows >= DEEP_SHORT_ROWS * n);
 }
+
+// The MXFP8 up/gate product's kept pre-activations (fp32, two values per element
+// of H) go past the L2, as every other output (gemm_mx.hip).  Not where they fit
+// the Infinity Cache beside little else: a short K loop then waits for these
+// stores, and past the L2 they run at 2.4 TB/s instead of 3.5.  Forward that keeps
+// them, past / through the L2 (us): d 256, 1500 rows of 8 experts, f 1024 (98 MB)
+// 87 / 79, f 2048 (197 MB) 139 / 124; d 512, f 1536 125 / 113; d 1024, f 1024 116 / 106,
+// f 2048 189 / 186; d 2048, f 1536 224 / 232.  Fewer rows (256 of 32 experts, d 1024,
+// f 1536: 122 / 134), smaller (49 MB, d 256: 56 / 58) and larger (393 MB, d 512: 0.92
+// of the time) are faster past it.
+inline bool mx_keep_l2(long R, long E, long K, long N) {
+    const long bytes = 8 * R * N;
+    return K <= 1024 && R >= 1024 * E && bytes >= (64L << 20) && bytes <= (208L << 20);
+}

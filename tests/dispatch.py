@@ -26,6 +26,7 @@ int t_skinny_tiles(long T, long k, long E, long f, long fs) { return skinny_tile
 int t_skinny_kslices(long T, long k, long E, long d, long f, long fs) {
     return skinny_kslices(T, k, E, d, f, fs, skinny_tiles(T, k, E, f, fs)); }
 int t_route_direct(long T, long d, long E, long k) { return route_direct(T, d, E, k); }
+int t_mx_keep_l2(long R, long E, long K, long N) { return mx_keep_l2(R, E, K, N); }
 int t_deep_stages(long K, long rows, long groups) { return deep_stages(K, rows, groups); }
 }
 """
@@ -70,6 +71,11 @@ def route_direct(T, d, E, k):
 def deep_stages(K, rows, groups):
     """A row product in a launch of its own holds three LDS stages of B instead of two."""
     return bool(_call("t_deep_stages", K, rows, groups))
+
+
+def mx_keep_l2(R, E, K, N):
+    """The MXFP8 up/gate product stores its kept pre-activations through the L2."""
+    return bool(_call("t_mx_keep_l2", R, E, K, N))
 
 
 def tile_shapes(tiles, K, rows, groups):

@@ -131,3 +131,14 @@ def test_third_stage_bounds():
     assert dispatch.deep_stages(768, 1024 * 3, 3) and not dispatch.deep_stages(768, 1024 * 3 + 1, 3)
     assert dispatch.deep_stages(512, 600, 3) and not dispatch.deep_stages(512, 599, 3)
     assert not dispatch.deep_stages(256, 600, 3) and dispatch.deep_stages(768, 1, 0)
+
+
+@pytest.mark.parametrize("d,f,E,rows,past,through", [
+    (256, 512, 8, 6000, 150, 136), (256, 1024, 8, 1500, 87, 79), (256, 2048, 8, 1500, 139, 124), (512, 512, 32, 1500, 159, 157),
+    (512, 1536, 8, 1500, 125, 113), (1024, 1024, 8, 1500, 116, 106), (1024, 2048, 8, 1500, 189, 186),
+    (256, 512, 8, 1500, 56, 58), (512, 2048, 32, 256, 116, 122), (1024, 1536, 32, 256, 122, 134),
+    (512, 1536, 32, 1500, 0.86, 1), (512, 1024, 8, 6000, 0.99, 1), (1024, 2048, 8, 6000, 0.93, 1),
+    (2048, 1536, 8, 1500, 224, 232), (2048, 2048, 8, 1500, 263, 272),
+])
+def test_mx_kept_activations(d, f, E, rows, past, through):
+    assert dispatch.mx_keep_l2(rows * E, E, d, f) == (through < past)

@@ -14,6 +14,7 @@ from oracle import mx_oracle as M
 from paper_2609_36070_amd import binding as B
 from paper_2609_36070_amd.layer import DeviceLayer
 from paper_2609_36070_amd.workloads import WORKLOADS, Workload, make_inputs, to_bf16
+from tests import dispatch
 from tests.parity import assert_close, check_route_and_plan, say, to_np, weights_dict
 
 pytestmark = pytest.mark.gpu
@@ -174,3 +175,26 @@ def test_mx_full_size_sampled():
             hh = M.mx_qdq(h[None, :], axis=1)[0]
             ref[n] += w_orc[t, s] * (Wd[e] @ hh)
     assert_close("Y (sampled tokens)", Y, ref)
+
+
+def test_kept_activations_through_and_past_the_l2():
+    """The kept pre-activations are the same bits whichever way they are stored
+    (dense routing: token t of expert e is plan row e T + t)."""
+    big = Workload("kept", T=8200, d=256, E=2, k=2, f=512, backward=True)
+    small = big.scaled(T=4000)
+    assert dispatch.mx_keep_l2(big.T * 2, 2, big.d, big.f) and not dispatch.mx_keep_l2(small.T * 2, 2, small.d, small.f)
+    inp = make_inputs(big, 3)
+    got = []
+    for w in (big, small):
+        say(f"[gpu] {w.name} T={w.T} d={w.d} f={w.f}")
+        L = DeviceLayer(w, dict(inp, X=inp["X"][:w.T], dY=inp["dY"][:w.T]), mx=True)
+        L.ws.fill_(0xA5)
+        L.route()
+        L.plan()
+        L.forward_mx()
+        torch.cuda.synchronize()
+        got.append([L.mx_ws_tensor(r, torch.float32, (2, w.T, w.f))[:, :small.T].clone() for r in (B.WS_AF, B.WS_BF)])
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    ref = M.mx_qdq(inp["X"][:64].astype(np.float64), 1) @ M.mx_qdq(inp["W_gate"][1].astype(np.float64), 0)
+    assert_close("A", to_np(got[0][0][1, :64]), ref)
