@@ -345,7 +345,7 @@ __global__ __launch_bounds__(512) void route_split_kernel(const uint16_t *__rest
                                                           float *__restrict__ topk_w,
                                                           float *__restrict__ part,
                                                           int T, int d, int E, int k, int S) {
-    static_assert(EPAD == 64 || EPAD == 128 || EPAD == 256, "split router: 64, 128 or 256 experts");
+    static_assert(EPAD == 128 || EPAD == 256, "split router: 128 or 256 padded experts");
     constexpr int TN = EPAD / 64;                         // 32-wide expert tiles per wave
     constexpr int XT = RT * 64, WT = EPAD * 64;           // stage elements (bf16)
     // stages of the chunk pipeline (NST - 1 chunks in flight): 4, or 3 where
@@ -661,10 +661,6 @@ hipError_t launch_route(const uint16_t *X, const uint16_t *W_r, const float *bia
     if (S > 0) {
         const dim3 grid((unsigned)(((T + RT - 1) / RT) * S)), block(512);
         switch (EPAD) {
-            case 64:
-                route_split_kernel<64><<<grid, block, 0, st>>>(X, WrT, bias, logits, topk_idx, topk_w,
-                                                               part, T, d, E, k, S);
-                break;
             case 128:
                 route_split_kernel<128><<<grid, block, 0, st>>>(X, WrT, bias, logits, topk_idx, topk_w,
                                                                 part, T, d, E, k, S);
@@ -680,9 +676,6 @@ hipError_t launch_route(const uint16_t *X, const uint16_t *W_r, const float *bia
 #define ROUTE_REDUCE(EP, SL) \
     route_reduce_kernel<EP, SL><<<rg, rb, 0, st>>>(part, bias, logits, topk_idx, topk_w, T, E, k)
             switch (EPAD * 16 + S) {
-                case 64 * 16 + 2: ROUTE_REDUCE(64, 2); break;
-                case 64 * 16 + 4: ROUTE_REDUCE(64, 4); break;
-                case 64 * 16 + 8: ROUTE_REDUCE(64, 8); break;
                 case 128 * 16 + 2: ROUTE_REDUCE(128, 2); break;
                 case 128 * 16 + 4: ROUTE_REDUCE(128, 4); break;
                 case 128 * 16 + 8: ROUTE_REDUCE(128, 8); break;
