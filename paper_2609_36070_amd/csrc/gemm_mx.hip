@@ -99,7 +99,8 @@ DEV i32x8_t frag(const uint8_t *t, int r0, int ks, int lane) {
                    (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
 }
 
-template <int MODE>
+// KEEP_L2: MX_UP stores the kept pre-activations through the L2 (mx_keep_l2).
+template <int MODE, bool KEEP_L2 = false>
 __global__ __launch_bounds__(NTHREADS, 1) void gemm_mx_kernel(MxGemmArgs g, const int *__restrict__ a_rows) {
     // one LDS object for both stages of both operands: the K loop picks the
     // stage by a wave-uniform offset at run time (see there)
@@ -400,7 +401,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void gemm_mx_kernel(MxGemmArgs g, cons
                         if (g.Sa) {   // pre-activations for the backward, fp32
                             float *sa = g.Sa + (long)p * g.N + fcol0 + c;
                             float *sb = g.Sb + (long)p * g.N + fcol0 + c;
-                            if (g.keep_l2) {
+                            if constexpr (KEEP_L2) {
                                 st_f32x8(sa, a);
                                 st_f32x8(sb, b);
                             } else {
@@ -554,13 +555,13 @@ __global__ __launch_bounds__(NTHREADS, 1) void gemm_mx_kernel(MxGemmArgs g, cons
     }
 }
 
-template <int MODE>
+template <int MODE, bool KEEP_L2 = false>
 hipError_t launch_mx_mode(MxGemmArgs g, int tiles_m, int ntn, hipStream_t st) {
     const long tiles = (long)tiles_m * ntn;
     if (tiles <= 0) return hipSuccess;
     g.tiles_m = tiles_m;
     const unsigned grid = (unsigned)raster_grid(tiles_m, ntn);
-    gemm_mx_kernel<MODE><<<dim3(grid), dim3(NTHREADS), 0, st>>>(g, g.a_rows);
+    gemm_mx_kernel<MODE, KEEP_L2><<<dim3(grid), dim3(NTHREADS), 0, st>>>(g, g.a_rows);
     return hipGetLastError();
 }
 
@@ -568,9 +569,10 @@ int mx_mtiles(long rows, int groups) { return (int)(rows / BM + (groups > 0 ? gr
 
 }  // namespace
 
-hipError_t launch_gemm_mx_up(MxGemmArgs g, long rows, int groups, hipStream_t st) {
-    g.keep_l2 = mx_keep_l2(rows, groups, g.K, g.N);
-    return launch_mx_mode<MX_UP>(g, mx_mtiles(rows, groups), g.N / (BN / 2), st);
+hipError_t launch_gemm_mx_up(const MxGemmArgs &g, long rows, int groups, hipStream_t st) {
+    const int tm = mx_mtiles(rows, groups), ntn = g.N / (BN / 2);
+    return g.Sa && mx_keep_l2(rows, groups, g.K, g.N) ? launch_mx_mode<MX_UP, true>(g, tm, ntn, st)
+                                                      : launch_mx_mode<MX_UP>(g, tm, ntn, st);
 }
 hipError_t launch_gemm_mx_down(const MxGemmArgs &g, long rows, int groups, hipStream_t st) {
     return launch_mx_mode<MX_DOWN>(g, mx_mtiles(rows, groups), g.N / BN, st);

@@ -202,7 +202,6 @@ struct MxGemmArgs {
     float *Cf3 = nullptr;              //   gradients read them)
     float *Sa = nullptr;               // MX_UP: keep the gate / up pre-activations (fp32)
     float *Sb = nullptr;
-    int keep_l2 = 0;                   // set by the launcher: through the L2 (mx_keep_l2)
     const float *E1 = nullptr;         // MX_DGRAD: saved pre-activations A, B (fp32)
     const float *E2 = nullptr;
     const float *rowscale = nullptr;   // MX_DGRAD: router weight per row
@@ -220,7 +219,7 @@ struct MxGemmArgs {
     // once, as expert 0's range, and read from position 0 for every expert
     int a_shared = 0, b_shared = 0;
 };
-hipError_t launch_gemm_mx_up(MxGemmArgs g, long rows, int groups, hipStream_t st);
+hipError_t launch_gemm_mx_up(const MxGemmArgs &g, long rows, int groups, hipStream_t st);
 hipError_t launch_gemm_mx_down(const MxGemmArgs &g, long rows, int groups, hipStream_t st);
 hipError_t launch_gemm_mx_dgrad(const MxGemmArgs &g, long rows, int groups, hipStream_t st);
 hipError_t launch_gemm_mx_dx(const MxGemmArgs &g, long rows, int groups, hipStream_t st);
