@@ -92,11 +92,17 @@ inline long raster_grid_groups(long tiles_m, int ntn) {
 // so an expert's chunks go to different XCDs.  (Numbering 4 x 4 blocks with
 // room for missing tiles gave some XCDs only partial blocks: at 16 x 6 tiles
 // per expert four XCDs ran 16 rounds and four ran 8.)
+// What is left after the whole rounds goes in chunks of 4: a window of the
+// bounded-memory backward has rows for some of the experts only, and contiguous
+// shares left it on few XCDs (4 of 12 experts of 6 tiles, three products: 27 tiles
+// on each of three XCDs, some CUs two deep; the launch 338 us, now 190).
 constexpr int WG_STRIP = 4, WG_CHUNK = 16;
 DEV bool map_tile_wgrad(int b, int groups, int ntm, int ntn, int &cm, int &nt) {
     const int per = ntm * ntn;
-    const int t = deal_tile(b, groups * per, WG_CHUNK);
+    const int n = groups * per, full = n / (8 * WG_CHUNK) * (8 * WG_CHUNK);
+    int t = b < full ? deal_tile(b, full, WG_CHUNK) : deal_tile(b - full, n - full, WG_STRIP);
     if (t < 0) return false;
+    if (b >= full) t += full;
     const int e = t / per, i = t % per;
     const int whole = ntn / WG_STRIP * WG_STRIP;       // n-tiles in strips of 4
     const int strip = i < whole * ntm ? i / (WG_STRIP * ntm) : whole / WG_STRIP;
@@ -107,5 +113,11 @@ DEV bool map_tile_wgrad(int b, int groups, int ntm, int ntn, int &cm, int &nt) {
     return true;
 }
 
-// Workgroups of a launch whose tiles map_tile_wgrad places.
-inline long wgrad_grid(long groups, int ntm, int ntn) { return deal_grid(groups * ntm * ntn, WG_CHUNK); }
+// Workgroups of a launch whose tiles map_tile_wgrad places, and no more of the
+// last round than have one: several products follow each other in a launch, and
+// places without a tile between them put one product's tiles on the same shader
+// engines as the last one's.
+inline long wgrad_grid(long groups, int ntm, int ntn) {
+    const long n = groups * ntm * ntn, rounds = n / (8 * WG_CHUNK);
+    return 8 * (rounds * WG_CHUNK + (n - rounds * 8 * WG_CHUNK + 7) / 8);
+}
