@@ -99,15 +99,23 @@ inline int skinny_kslices(long T, long k, long E, long d, long f, long fs, long 
 // 2048, d 256: 8192 tokens 1194 / 636; 8 of 256, d 1024: 2048 tokens 84 / 68,
 // 8192 125 / 203; 2 of 256, d 256: 30000 tokens 49 / 71; over 306 shapes of 2
 // to 16 experts the line is at most 10 % off the better side.
+// Up to 64 tiles of Y a product of its own runs in quarter tiles, which the folded
+// one cannot, in about two thirds of the time; that is all there is to gain with
+// one expert, and for the shared expert's part of the chain: 1 expert of 2048, d
+// 256: 300 tokens 62 / 34, 16000 138 / 122; of 512, d 1024: 2000 tokens 33.6 / 32.2,
+// 4000 36 / 40; of 256, d 256, and a shared one of 1024: 2000 tokens 53 / 45, 16000
+// 99 / 101; 2 of 512 and one of 1024, d 1024: 2000 tokens 85 / 70.
 // Only up to half of the CUs' worth of Y tiles: past them the folded product
 // fills the chip itself.
 constexpr long DENSE_PARTS_MAX = 128, DENSE_PARTS_VALUES = 12000;
+constexpr long DENSE_QUARTER_MAX = 64, DENSE_QUARTER_VALUES = 4500;
 
 inline bool dense_parts(long T, long d, long E, long k, long f, long fs) {
     const long nt = (T + 255) / 256 * (d / 256);
     if (k != E || T <= 0 || nt > DENSE_PARTS_MAX) return false;
     const long rounds = (E * nt + 255) / 256;
-    return (E + (fs > 0)) * T * d < DENSE_PARTS_VALUES * f * (E - rounds);
+    const long quarters = nt <= DENSE_QUARTER_MAX ? DENSE_QUARTER_VALUES * (fs + (E == 1 ? f : 0)) : 0;
+    return (E + (fs > 0)) * T * d <= DENSE_PARTS_VALUES * f * (E - rounds) + quarters;
 }
 
 // Experts padded to the routers' tiles.

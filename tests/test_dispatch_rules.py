@@ -17,6 +17,14 @@ pytestmark = pytest.mark.skipif(not dispatch.HAVE_CXX, reason="needs a host comp
     (500, 2048, 16, 768, 1024, 405, 155), (4000, 2048, 16, 768, 1024, 706, 848), (2800, 2816, 2, 256, 512, 85, 131),
     (1536, 4096, 8, 256, 0, 140, 205), (512, 4096, 16, 2048, 0, 988, 430), (1000, 7168, 2, 256, 0, 76, 91),
     (200, 7168, 8, 2048, 2048, 706, 387), (500, 7168, 4, 2048, 2048, 493, 355),
+    # one expert, and a shared expert longer than the others
+    (1, 2048, 1, 1536, 0, 55.1, 38.7), (300, 256, 1, 2048, 0, 61.7, 33.8), (16000, 256, 1, 2048, 0, 138, 122),
+    (16000, 256, 1, 256, 0, 29, 42.8), (2000, 1024, 1, 512, 0, 33.6, 32.2), (4000, 1024, 1, 512, 0, 36.2, 40.0),
+    (1000, 4096, 1, 512, 0, 55.5, 58.6), (1000, 4096, 1, 2048, 0, 94.1, 80.0), (2000, 4096, 1, 2048, 0, 142, 154),
+    (1000, 7168, 1, 2048, 2048, 208, 234), (300, 7168, 1, 2048, 1024, 195, 170), (4000, 1024, 1, 512, 1024, 87.4, 89.1),
+    (2000, 1024, 1, 512, 1024, 71.6, 63.8), (4000, 256, 2, 256, 1024, 66.1, 56.3), (16000, 256, 2, 256, 1024, 112.7, 119.3),
+    (2000, 1024, 2, 512, 1024, 85.4, 69.9), (4000, 1024, 3, 512, 1024, 128.3, 123.2), (1000, 4096, 3, 512, 0, 82.0, 78.2),
+    (2000, 4096, 3, 512, 1024, 192.4, 239.7),
 ])
 def test_dense_down_products(T, d, E, f, fs, folded, parts):
     w = Workload("dense", T=T, d=d, E=E, k=E, f=f, f_s=fs)

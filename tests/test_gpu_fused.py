@@ -71,7 +71,7 @@ def assert_bitwise(ref, got):
 
 
 @pytest.mark.parametrize("w", [RAGGED_TRAIN,
-                               Workload("dense_shared_train", T=1111, d=2048, E=6, k=6, f=256,
+                               Workload("dense_shared_train", T=1211, d=2048, E=6, k=6, f=256,
                                         f_s=256, bias_std=0.5, backward=True)],
                          ids=lambda w: w.name)
 def test_fused_training_layer(w):

@@ -113,6 +113,7 @@ def test_ring_edge_shapes(w, ring_rows):
     Workload("small_slices", T=3, d=4352, E=3, k=3, f=256, f_s=512),      # K slices
     Workload("parts", T=130, d=512, E=9, k=9, f=512, f_s=256),            # fp32 products, then their sum
     Workload("parts_no_shared", T=70, d=256, E=3, k=3, f=1024),
+    Workload("parts_one", T=70, d=256, E=1, k=1, f=1024, f_s=256),
     Workload("folded_few", T=2000, d=2816, E=2, k=2, f=256, f_s=512),     # one folded product
     Workload("folded_many", T=2900, d=2816, E=2, k=2, f=256),
 ], ids=lambda w: w.name)

@@ -49,6 +49,7 @@ def test_small_batch_parity(w):
     # then the same with the activations kept
     (Workload("parts", T=1500, d=1024, E=4, k=4, f=512, f_s=512), True),
     (Workload("parts_rounds", T=1200, d=1024, E=16, k=16, f=256), True),
+    (Workload("parts_one", T=600, d=512, E=1, k=1, f=512, f_s=256), True),
     (Workload("folded_121", T=2800, d=2816, E=2, k=2, f=256, f_s=512), False),
     (Workload("folded", T=2900, d=2816, E=2, k=2, f=256, f_s=512), False),
     (Workload("parts_train", T=130, d=512, E=9, k=9, f=256, backward=True), True),
