@@ -1,6 +1,7 @@
 // Which path a forward takes: rules on sizes alone, host code without HIP.
 #pragma once
 
+#include <algorithm>
 #include <cmath>
 #include <cstddef>
 
@@ -42,18 +43,19 @@ inline long skinny_slots(long R, long E, long bm) { return (R < E ? R : E) + R /
 // each) run in rounds of the 256 CUs, so 288 of them (8 experts and a shared one
 // of 2048 columns) take as long as 512.  K is split over two or four where that
 // ends the launch earlier, if each slice keeps 1024 rows; the SwiGLU then moves to
-// a launch of its own (4 us), the slices are at most four or five rounds and their
-// sums take at most SK_SLICE_BYTES.
+// a launch of its own (4 us), the slices are at most five rounds and their sums
+// take at most SK_SLICE_BYTES.
 //
 // Workgroups are counted for the experts that T balanced tokens reach, with a
-// tenth for the ones they reach beyond that.  Slices that just fit one round do
+// tenth for the ones they reach beyond that (if there are any left).  Slices that just fit one round do
 // so only where the launch has no spare workgroups: those end at once and leave
 // their CU to a second one.
 //
 // Forward at 1 / 2 / 4 slices (us), by workgroups: 16, d 5120: 36 / - / 25; 64, d
 // 4096: 56 / 45 / 41; 96, d 2048: 32.5 / 30.2; 112, d 4096: 60 / 50 / 52; 128, d 2048:
 // 40 / 37, with spare ones 42 / 45; 148, d 4096: 62 / 65 / 56; 288, d 7168: 1 token
-// 186 / 169 / 160, 61 tokens 242 / 214 / 206; 344, d 7168: 186 / 175.  As many rounds
+// 186 / 169 / 160, 61 tokens 242 / 214 / 206; 344, d 7168: 186 / 175; 592, d
+// 6144: whole call 326 / 315.  As many rounds
 // either way: 175, d 4096: 71 / 82 / 78; 210: 73 / 70 / 79; 256: 92 / 96 / 100; 444: 139 /
 // 144; 493, d 2048: 73 / 78.
 constexpr long SK_SPLIT_MAX = 4;
@@ -71,11 +73,12 @@ inline int skinny_kslices(long T, long k, long E, long d, long f, long fs, long 
     if (reached < R / bm) reached = (double)(R / bm);
     const long wgs = (long)std::ceil(reached * (f / 64) - 1e-6) + shared;
     const long grid = skinny_slots(R, E, bm) * (f / 64) + shared;
+    const long most = T <= bm ? (R < E ? R : E) * (f / 64) + shared : grid;   // T rows: one tile per expert
     long best = 1, rounds = (wgs + 255) / 256;        // of `best` slices each
     for (long s = 2; s <= skinny_max_slices(d); s *= 2) {
         const long n = wgs * s;
-        if (wgs > (s == 2 ? 512 : 320) || 8 * (size_t)s * ((size_t)R * f + (size_t)T * fs) > SK_SLICE_BYTES) break;
-        const long r = n <= 252 || (n <= 256 && grid * s <= 256) ? 1 : (n + n / 10 + 255) / 256;
+        if (wgs >= (s == 2 ? 640 : 320) || 8 * (size_t)s * ((size_t)R * f + (size_t)T * fs) > SK_SLICE_BYTES) break;
+        const long r = n <= 252 ? 1 : n <= 256 ? 1 + (grid * s > 256) : (std::min(n + n / 10, most * s) + 255) / 256;
         if (r * best < rounds * s) {
             best = s;
             rounds = r;

@@ -69,7 +69,8 @@ def test_small_batches_bounds():
     (4, 4096, 8, 2, 2048, 0, (70, 82, 76)), (24, 4096, 8, 2, 2048, 0, (88, 92, 94)), (61, 4096, 8, 2, 2048, 0, (93, 96, 101)),
     (8, 7168, 64, 8, 512, 512, (186, 175)), (16, 7168, 64, 8, 512, 512, (230, 234)),
     (2, 5120, 200, 2, 512, 0, (56, 40, 33)), (24, 5120, 200, 2, 512, 0, (138, 129)),
-    (16, 3072, 8, 2, 2048, 0, (65.8, 70)), (4, 2048, 16, 16, 1024, 1024, (65.7, 63)),
+    (16, 3072, 8, 2, 2048, 0, (65.8, 70)), (28, 6144, 24, 8, 1536, 1024, (326, 315)),
+    (51, 4864, 8, 4, 2048, 0, (132, 141)), (4, 2048, 16, 16, 1024, 1024, (65.7, 63)),
 ])
 def test_small_batch_slices(T, d, E, k, f, fs, us):
     w = Workload("small", T=T, d=d, E=E, k=k, f=f, f_s=fs)
@@ -84,7 +85,8 @@ def test_small_batch_slices_bounds():
     assert dispatch.kslices(one.scaled(f=64 * 128)) == 2      # 128 workgroups: one round of slices
     assert dispatch.kslices(one.scaled(f=64 * 132)) == 1      # two rounds of slices
     assert dispatch.kslices(one.scaled(f=64 * 260)) == 2      # two rounds, three of slices
-    assert dispatch.kslices(one.scaled(f=64 * 516)) == 1
+    assert dispatch.kslices(one.scaled(f=64 * 516)) == 2      # three rounds, five of slices
+    assert dispatch.kslices(one.scaled(f=64 * 640)) == 1
     for f, slices in ((64 * 288, 4), (64 * 320, 2), (64 * 344, 2), (64 * 388, 1)):    # as many rounds at two and at four
         assert dispatch.kslices(one.scaled(d=4096, f=f)) == slices
 
